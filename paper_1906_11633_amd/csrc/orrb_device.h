@@ -123,6 +123,7 @@ struct GradArgs {
     const int64_t *gitem_pbase;      // first partial (double) of each item
     int32_t n_gitems;
     double *partial;                 // per item: 5 per object, 4 per light, 1 exposure
+    int32_t *live;                   // per item: 1 if it shows a fragment (else its partial is unwritten)
     const int32_t *scene_frames, *scene_frame_begin;  // frames of each scene (CSR)
     const int32_t *frame_item_begin;                  // [F+1] item range of each frame
     const int32_t *obj_scene, *obj_local, *light_scene, *light_local;

@@ -495,7 +495,7 @@ static orrb_status upload_grad_tables(orrb_layout *L) {
 
 static size_t grad_workspace(const orrb_layout *L) {
     return al256(ws_layout(L->all_vertex_instances, L->all_object_instances).total) +
-           al256(sizeof(double) * (size_t)L->grad_partials);
+           al256(sizeof(double) * (size_t)L->grad_partials) + al256(sizeof(int32_t) * L->gitems.size());
 }
 
 static orrb_status upload_layout(orrb_layout *L) {
@@ -1208,6 +1208,7 @@ orrb_status orrb_shade_backward(orrb_context *ctx, const orrb_layout *L, const o
     g.gitem_pbase = L->gtab.at<int64_t>(L->g_gitem_pbase);
     g.n_gitems = (int32_t)L->gitems.size();
     g.partial = (double *)(ws + al256(w.total));
+    g.live = (int32_t *)(ws + al256(w.total) + al256(sizeof(double) * (size_t)L->grad_partials));
     g.scene_frames = L->gtab.at<int32_t>(L->g_scene_frames);
     g.scene_frame_begin = L->gtab.at<int32_t>(L->g_scene_frame_begin);
     g.frame_item_begin = L->gtab.at<int32_t>(L->g_frame_item_begin);
