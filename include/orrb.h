@@ -147,7 +147,10 @@ typedef struct {
  * vertices, <= 48 objects, < 65536 triangles) and, with path 2, also larger scenes
  * (<= 65536 vertices, <= 127 objects, < 65536 triangles) whose snapped vertices, bins
  * and survivors then live in workspace scratch; every triangle is set up once per
- * frame either way.  Other frames go through the tiled path (a vertex kernel, then one
+ * frame either way.  Frames of scenes that fit in LDS are cut into rectangles for the
+ * patch kernel (a workgroup renders one) where that is faster: batches of fewer frames
+ * than occupy the chip, a uniform batch's last partly filled round, and frames larger
+ * than 256x256.  Other frames go through the tiled path (a vertex kernel, then one
  * workgroup per screen tile). */
 typedef struct {
     int32_t tile_w, tile_h;  /* tiled path: tile size, each in {16, 32, 64} */
@@ -156,8 +159,8 @@ typedef struct {
                                 per triangle of the largest scratch-held scene (more: a frame falls
                                 back to scanning every triangle per tile, same bits) */
     int32_t persistent;      /* tiled path: 1 = persistent grid pulling tiles from a device queue */
-    int32_t path;            /* 0 = frame kernel where the scene fits in LDS, 1 = tiled path for
-                                every frame, 2 = frame kernel for every frame it can take */
+    int32_t path;            /* 0 = frame or patch kernel where the scene fits in LDS, 1 = tiled path
+                                for every frame, 2 = these kernels for every frame they can take */
 } orrb_tuning;
 
 typedef struct {
@@ -166,14 +169,16 @@ typedef struct {
     int64_t vertex_instances;   /* sum over frames of the frame's scene vertex count */
     int64_t triangle_instances; /* sum over frames of the frame's scene triangle count */
     int64_t tile_items;         /* tiled-path work items with the current tuning */
-    int64_t frame_path_frames;  /* frames rendered by the frame kernel with the current tuning */
+    int64_t frame_path_frames;  /* frames rendered by the frame or patch kernel with the current tuning */
     size_t workspace_bytes;      /* workspace orrb_render_batch needs (current tuning) */
     size_t workspace_bytes_any;  /* workspace enough for every valid tuning */
     size_t grad_workspace_bytes; /* workspace orrb_shade_backward needs */
     size_t table_bytes;          /* device memory the layout itself holds (its tables) */
     orrb_tuning tuning;
     int64_t render_kernels;      /* kernel launches one orrb_render_batch makes (current tuning,
-                                    shadow frames included): a captured graph's kernel nodes */
+                                    shadow frames included): a captured graph's kernel nodes (a call
+                                    with a stats or track destination that renders patches makes one
+                                    more per set of patches) */
 } orrb_layout_info;
 
 /* Validate `desc` against the context's meshes and build a layout (device tables are
@@ -298,6 +303,8 @@ typedef struct {
 /* Counters of one render call, written by its kernels into caller memory (the
  * `stats` destination of orrb_outputs).  The kernels ADD to the words, so a caller
  * zeroes the buffer before the call for per-call counts, or keeps adding across calls.
+ * Frames rendered as patches count like the frame kernel's (words 1 and 2 when the
+ * frame as a whole would have passed its limits).
  * They are ordinary device memory: read them with a copy on the call's stream (no
  * device-wide synchronization).  Word meanings: */
 #define ORRB_STAT_WAIT_TIMEOUTS     0  /* frame-kernel waits that reached their bound; the
@@ -378,8 +385,9 @@ orrb_status orrb_validate_batch(orrb_context *ctx, const orrb_layout *layout, co
  * by the caller; consecutive calls on one stream are safe.  Errors: as
  * orrb_render_batch, plus ORRB_ERR_UNSUPPORTED (with nothing enqueued) when the
  * batch needs more workspace than the array holds (orrb_layout_info.workspace_bytes
- * > ORRB_NOALLOC_SCRATCH_BYTES; the frame path needs a few hundred bytes, the tiled
- * path 16 bytes per vertex instance plus 64 per object instance). */
+ * > ORRB_NOALLOC_SCRATCH_BYTES; the frame path needs a few hundred bytes, 8 bytes per
+ * frame more when it renders patches, the tiled path 16 bytes per vertex instance plus
+ * 64 per object instance). */
 #define ORRB_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)
 orrb_status orrb_render_batch_noalloc(orrb_context *ctx, const orrb_layout *layout, const orrb_scenes *scenes,
                                       const orrb_cameras *cameras, const orrb_params *params,
@@ -461,7 +469,7 @@ orrb_status orrb_shade_backward(orrb_context *ctx, const orrb_layout *layout, co
 typedef struct {
     double vertex_ms;          /* summed device time of k_vertex launches (tiled path) */
     double raster_ms;          /* summed device time of k_raster_shade launches (tiled path) */
-    double frame_ms;           /* summed device time of k_frame launches (frame path) */
+    double frame_ms;           /* summed device time of the frame path's launches (k_frame, k_patch) */
     int64_t vertex_launches, raster_launches, frame_launches;
 } orrb_kernel_times;
 

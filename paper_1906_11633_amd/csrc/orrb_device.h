@@ -37,6 +37,15 @@ struct ObjInfo {
     int32_t mesh_tbegin, n_tris;   // triangle range in the mesh pool
     int32_t scene_vbase;           // vertex offset inside its scene's block
     int32_t scene_tbase;           // scene-local triangle ID of its first triangle
+    int32_t mesh;                  // its mesh (bounding box in mesh_box)
+};
+
+// Work item of k_patch: the pixels [x0, x1) x [y0, y1) of a frame (at most
+// patch_max_pixels() of them); parts: the frame's patches.
+struct PatchItem {
+    int32_t frame;
+    uint16_t x0, y0, x1, y1;
+    int32_t parts;
 };
 
 struct RenderArgs {
@@ -46,6 +55,10 @@ struct RenderArgs {
     const int2 *vitems;     // (frame, object-in-scene) work items of k_vertex
     const int2 *titems;     // (frame, tile) work items of k_raster_shade
     const int32_t *fitems;  // frames rendered by k_frame
+    const PatchItem *pitems;  // rectangles of frames rendered by k_patch
+    int32_t n_pitems;
+    int32_t p_side, p_bin_max, p_surv_max;  // the frame kernel's limits, for the call's counters
+    unsigned long long *p_account;   // per frame: sums of its patches (patch_account), or null
     const int32_t *light_type;
     int32_t n_vitems, n_titems, n_fitems;
     int32_t f_grid;         // frame kernel grid: workgroup b starts with fitems[b]
@@ -57,6 +70,7 @@ struct RenderArgs {
     const float4 *mesh_pos;  // xyz, 0
     const float4 *mesh_nrm;  // xyz, 0
     const int4 *mesh_tri;    // local vertex indices, 0
+    const float *mesh_box;   // [6] per mesh: least and largest coordinates (object space)
     // scenes
     const float *pose;
     const int32_t *seg;
@@ -160,8 +174,12 @@ hipError_t launch_shadow_cams(const int32_t *spot_light, int n_spot, const float
 hipError_t launch_validate(const RenderArgs &a, const float *post, int n_obj, int n_lights, int n_frames,
                            uint32_t *stats, hipStream_t stream);
 hipError_t read_wait_timeouts(unsigned int *out);  // frame-kernel waits that hit their bound
-bool frame_fits(int n_verts, int n_obj, int n_tris, int width, int height);
-bool frame_fits_global(int64_t n_verts, int n_obj, int64_t n_tris, int width, int height);
+hipError_t launch_patch(const RenderArgs &a, hipStream_t stream);
+bool frame_fits(int64_t n_verts, int n_obj, int64_t n_tris);       // scenes held in LDS
+bool frame_fits_global(int64_t n_verts, int n_obj, int64_t n_tris);  // in the frame kernel's scratch
+int frame_max_side();                                                // frames up to this wide and high
+void frame_limits(int *bin_max, int *surv_max);
+int patch_max_pixels();
 size_t raster_lds_bytes(int tile_w, int tile_h, int bin_cap);
 // render call shared by orrb_render_batch and orrb_render_batch_noalloc (orrb_host.cpp)
 orrb_status debug_validate(orrb_context *ctx, const orrb_layout *L, const orrb_scenes *sc, const orrb_cameras *cam,

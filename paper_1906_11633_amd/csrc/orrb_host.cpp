@@ -4,7 +4,7 @@
 // uploaded once and shared by every scene instance).  A layout owns the device tables
 // describing one batch structure (which meshes each scene uses, frame sizes, tile and
 // vertex work items); building it validates every host-visible argument, so a render
-// call only checks pointers and the workspace size before enqueueing two kernels.
+// call only checks pointers and the workspace size before enqueueing its kernels.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -55,14 +55,25 @@ struct DevBuf {
     ~DevBuf() {
         if (p) (void)hipFree(p);
     }
-    hipError_t upload(const void *src, size_t n) {
+    // spare: allocate at least that much (a pool that grows mesh by mesh)
+    hipError_t upload(const void *src, size_t n, size_t spare = 0) {
         if (n > bytes) {
             if (p) (void)hipFree(p);
             p = nullptr;
             bytes = 0;
-            hipError_t e = hipMalloc(&p, n);
-            if (e != hipSuccess) return e;
-            bytes = n;
+            const size_t want = n > spare ? n : spare;
+            bytes = want;
+            hipError_t e = hipMalloc(&p, want);
+            if (e != hipSuccess && want > n) {
+                (void)hipGetLastError();
+                bytes = n;
+                e = hipMalloc(&p, n);
+            }
+            if (e != hipSuccess) {
+                p = nullptr;
+                bytes = 0;
+                return e;
+            }
         }
         if (n == 0) return hipSuccess;
         return hipMemcpy(p, src, n, hipMemcpyHostToDevice);
@@ -150,7 +161,8 @@ struct orrb_context {
     std::vector<float4> pos, nrm;
     std::vector<int4> tri;
     std::vector<int32_t> mesh_vbegin{0}, mesh_tbegin{0};
-    DevBuf d_pos, d_nrm, d_tri;
+    std::vector<float> mesh_box;  // per mesh: least and largest coordinates
+    DevBuf d_pos, d_nrm, d_tri, d_box;
     // per-vertex texture coordinates of the pool (0 until orrb_set_mesh_uv) and the
     // resident pattern textures (RGB texels as float4, per texture: first texel, w, h)
     std::vector<float2> uv;
@@ -181,11 +193,14 @@ struct orrb_layout {
     int64_t gframes = 0, gf_verts = 0, gf_tris = 0;
     std::vector<int2> vitems, titems;
     std::vector<int32_t> fitems;  // frame-kernel schedule (see schedule_frames)
+    std::vector<PatchItem> pitems;  // patches (see schedule_patches)
+    int64_t p_frames = 0;          // frames rendered as patches
     int64_t f_frames = 0;          // frames on the frame kernel
     int32_t f_grid = 0;            // its persistent grid
     int32_t f_dynamic = 0;         // 1: frames claimed from a counter (uneven batch)
     std::vector<int32_t> light_type;
-    Packed tab;  // frames, objs, vitems, titems, fitems, light_type, spot tables
+    Packed tab;  // frames, objs, vitems, titems, fitems, pitems, light_type, spot tables
+    size_t o_pitems = 0;
     size_t o_frames = 0, o_objs = 0, o_vitems = 0, o_titems = 0, o_fitems = 0, o_light_type = 0;
     // spot lights (type 2) with shadow maps: one N x N depth frame per spot light, from
     // its shadow camera, rendered by a sub-layout before the frames themselves
@@ -222,7 +237,7 @@ struct orrb_layout {
 static size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct WsLayout {
-    size_t vtx_pos, obj_rot, obj_bbox, queue, fscratch, total;
+    size_t vtx_pos, obj_rot, obj_bbox, queue, account, fscratch, total;
     size_t fs_stride;
     int64_t fs_verts, fs_surv, fs_bins;
 };
@@ -248,7 +263,8 @@ static FrameScratch frame_scratch(int64_t gframes, int64_t frame_kernel_frames, 
     return f;
 }
 
-static WsLayout ws_layout(int64_t vertex_instances, int64_t object_instances, const FrameScratch &fs = FrameScratch()) {
+static WsLayout ws_layout(int64_t vertex_instances, int64_t object_instances, const FrameScratch &fs = FrameScratch(),
+                          int64_t patched_frames = 0) {
     WsLayout w;
     size_t off = 0;
     w.vtx_pos = off;
@@ -259,6 +275,8 @@ static WsLayout ws_layout(int64_t vertex_instances, int64_t object_instances, co
     off = al256(off + sizeof(int4) * (size_t)object_instances);
     w.queue = off;
     off = al256(off + 64);
+    w.account = off;  // 8 bytes per frame when some are rendered as patches
+    off = al256(off + sizeof(uint64_t) * (size_t)patched_frames);
     w.fscratch = off;
     w.fs_stride = fs.stride;
     w.fs_verts = fs.verts;
@@ -279,14 +297,20 @@ static bool valid_tuning(const orrb_tuning &t) {
     return raster_lds_bytes(t.tile_w, t.tile_h, t.bin_cap) <= 160 * 1024;
 }
 
+// Estimated work of frame f: triangles (half again when the scene data live in global
+// scratch) plus a quarter per pixel.
+static double frame_cost(const orrb_layout *L, int32_t f) {
+    const FrameInfo &fi = L->frames[f];
+    return (double)L->scene_tris[fi.scene] * (fi.mode ? 1.5 : 1.0) + 0.25 * (double)fi.width * fi.height;
+}
+
 // Schedule of the frame kernel's persistent grid (min(frames, CUs) workgroups).  A
 // uniform batch keeps the plain frame order and a static assignment: workgroup b
 // renders fitems[b], fitems[b + grid], ...  An uneven batch is sorted by estimated work,
 // heaviest first, and handed out at run time: workgroup b starts with fitems[b] and each
 // workgroup takes the next unclaimed frame from a counter as it finishes one, so the
 // workgroups end within about one light frame of each other whatever the estimate's
-// error.  Estimated work: triangles (half again when the scene data live in global
-// scratch) plus a quarter per pixel.
+// error.
 static void schedule_frames(orrb_layout *L) {
     const int64_t n = (int64_t)L->fitems.size();
     L->f_frames = n;
@@ -296,8 +320,7 @@ static void schedule_frames(orrb_layout *L) {
     std::vector<double> cost(n);
     bool uniform = true;
     for (int64_t k = 0; k < n; ++k) {
-        const FrameInfo &fi = L->frames[L->fitems[k]];
-        cost[k] = (double)L->scene_tris[fi.scene] * (fi.mode ? 1.5 : 1.0) + 0.25 * (double)fi.width * fi.height;
+        cost[k] = frame_cost(L, L->fitems[k]);
         uniform = uniform && cost[k] == cost[0];
     }
     if (uniform || n <= L->f_grid) return;
@@ -310,14 +333,135 @@ static void schedule_frames(orrb_layout *L) {
     L->f_dynamic = 1;
 }
 
+// Cut a frame into patches, a grid of columns (of whole 4-pixel units) and rows whose cells
+// hold at most patch_max_pixels().  More than the least number of patches are asked for
+// where they all run at once: the frame is cut into `parts` strips of its width (of 256
+// pixels or so of a wider frame), which share out what the middle of the frame shows.
+// Otherwise (batches of several rounds, where the geometry each patch repeats counts) into
+// the least number of columns, in two or more rows where a column would be narrower than 28
+// pixels: hand scenes, 120 frames of 200 x 200, 79 us in 7 columns and 85 us in 7 rows; 48
+// frames of 128 x 128, 33 us in 6 rows, 38 us in 2 x 3 cells.
+static void patch_grid(int W, int H, int parts, int *cols, int *rows) {
+    constexpr int U = 4;
+    const int nx = (W + U - 1) / U, cap = patch_max_pixels();
+    auto fits = [&](int x, int y) { return (int64_t)U * ((nx + x - 1) / x) * ((H + y - 1) / y) <= cap; };
+    int x = 1, y = 1;
+    for (y = 1; y <= H; ++y) {
+        for (x = 1; x < nx && !fits(x, y); ++x) {
+        }
+        if (fits(x, y) && (x == 1 || W >= 28 * x)) break;
+    }
+    if (y > H) y = H;  // (a column of one unit is always narrow enough: U * H rows <= cap at y = H)
+    if (parts > x * y) {
+        x = std::max(1, std::min(nx, (W + 128) / 256));
+        for (y = std::max(1, std::min(H, parts / x)); y < H && !fits(x, y); ++y) {
+        }
+    }
+    *cols = x;
+    *rows = y;
+}
+
+static void cut_frame(const FrameInfo &fi, int32_t f, int parts, std::vector<PatchItem> &out) {
+    int px, py;
+    patch_grid(fi.width, fi.height, parts, &px, &py);
+    const int nx = (fi.width + 3) / 4;
+    for (int y = 0; y < py; ++y)
+        for (int x = 0; x < px; ++x) {
+            PatchItem it{};
+            it.frame = f;
+            it.x0 = (uint16_t)(4 * ((int64_t)nx * x / px));
+            it.y0 = (uint16_t)((int64_t)fi.height * y / py);
+            it.x1 = (uint16_t)std::min<int64_t>(4 * ((int64_t)nx * (x + 1) / px), fi.width);
+            it.y1 = (uint16_t)((int64_t)fi.height * (y + 1) / py);
+            it.parts = px * py;
+            out.push_back(it);
+        }
+}
+
+// Move the frames that are better rendered as patches from `frames` (LDS-held scenes, in
+// order) to `patched`.  Frames beyond the frame kernel's 256 x 256 always are.  The frame
+// kernel renders one frame per CU and round and a batch takes as long as its longest; a
+// frame's patches together cost about 1.25 times a frame (they repeat geometry), or 0.75
+// times when one patch holds it (no staging, sixteen compute waves), but fill the chip.  So
+// the frames of a batch smaller than the chip are cut when that work, spread over the CUs,
+// takes less than the longest frame, and so are the frames of a uniform batch's last,
+// partly filled round.  Measured (one MI355X, hand scenes, us, frame kernel / patches): 12
+// frames of 200 x 200 108 / 23, 48: 110 / 44, 120: 117 / 76, 200: 120 / 122; 128 x 128: 48
+// frames 74 / 33, 200: 80 / 76; 64 x 64: 24 frames 50 / 20, 200: 53 / 39.
+static void choose_patches(const orrb_layout *L, std::vector<int32_t> &frames, bool scratch, std::vector<int32_t> &patched) {
+    const int64_t n_cu = L->ctx ? L->ctx->n_cu : 256;
+    const int side = frame_max_side();
+    std::vector<int32_t> rest;
+    double sum = 0.0, most = 0.0;
+    bool uniform = true;
+    for (int32_t f : frames) {
+        const FrameInfo &fi = L->frames[f];
+        if (fi.width > side || fi.height > side) {
+            patched.push_back(f);
+            continue;
+        }
+        const double c = frame_cost(L, f);
+        uniform = uniform && (rest.empty() || c == most);
+        sum += c * (fi.width * fi.height <= patch_max_pixels() ? 0.75 : 1.25);
+        most = std::max(most, c);
+        rest.push_back(f);
+    }
+    frames.clear();
+    const int64_t n = (int64_t)rest.size();
+    int64_t keep = n;  // frames that stay with the frame kernel
+    if (!scratch && n > 0) {
+        if (n <= n_cu || (uniform && sum <= 0.75 * n * most)) {
+            if (sum < (double)n_cu * most || sum <= 0.75 * n * most) keep = 0;
+        } else if (uniform && 1.25 * (double)(n % n_cu) < (double)n_cu) {
+            keep = n - n % n_cu;
+        }
+    }
+    frames.assign(rest.begin(), rest.begin() + keep);
+    patched.insert(patched.end(), rest.begin() + keep, rest.end());
+}
+
+// The patches: enough of them to fill the CUs a little more than once (twice for frames
+// beyond 256 x 256, whose outer patches are often empty), the costlier frames cut into more.
+static void schedule_patches(orrb_layout *L, const std::vector<int32_t> &patched) {
+    const int64_t n_cu = L->ctx ? L->ctx->n_cu : 256;
+    const int side = frame_max_side();
+    L->pitems.clear();
+    L->p_frames = (int64_t)patched.size();
+    double total = 0.0;
+    for (int32_t f : patched) total += frame_cost(L, f);
+    for (int32_t f : patched) {
+        const FrameInfo &fi = L->frames[f];
+        const double over = fi.width > side || fi.height > side ? 2.0 : 1.125;
+        cut_frame(fi, f, (int)(over * (double)n_cu * frame_cost(L, f) / total), L->pitems);
+    }
+    // The middle of a frame usually shows the most: patches nearest to their frame's centre
+    // first, so that the last ones to run are light, and the same patch of consecutive
+    // frames on consecutive XCDs (in frame order, eight patches a frame put all the middle
+    // ones on the same two XCDs: 120 hand frames of 200 x 200 in 8 rows, 136 us against 109).
+    std::vector<double> off(L->pitems.size());
+    std::vector<int32_t> order(L->pitems.size());
+    for (size_t k = 0; k < off.size(); ++k) {
+        const PatchItem &it = L->pitems[k];
+        const FrameInfo &fi = L->frames[it.frame];
+        off[k] = std::max(std::fabs((it.x0 + it.x1) / (double)fi.width - 1.0), std::fabs((it.y0 + it.y1) / (double)fi.height - 1.0));
+        order[k] = (int32_t)k;
+    }
+    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return off[x] < off[y]; });
+    std::vector<PatchItem> sorted(L->pitems.size());
+    for (size_t k = 0; k < order.size(); ++k) sorted[k] = L->pitems[order[k]];
+    L->pitems.swap(sorted);
+}
+
 // Kernel launches of one render call: the shadow frames' (camera gather + their own),
 // vertex + raster for the tiled path, the frame kernel (after a counter clear when its
-// frames are claimed at run time).
+// frames are claimed at run time), the patch kernel (with counters or Tracker records a call
+// launches one more before it).
 static int64_t render_kernels(const orrb_layout *L) {
     if (L->n_frames == 0) return 0;
     int64_t n = L->shadow ? 1 + render_kernels(L->shadow) : 0;
     if (!L->titems.empty()) n += 2;
     if (!L->fitems.empty()) n += 1 + L->f_dynamic;
+    if (!L->pitems.empty()) n += 1;
     return n;
 }
 
@@ -325,7 +469,7 @@ static WsLayout ws_layout(const orrb_layout *L) {
     const FrameScratch fs =
         frame_scratch(L->gframes, L->f_frames, L->gf_verts, L->gf_tris, L->tuning.bin_cap,
                       L->ctx ? L->ctx->n_cu : 256);
-    return ws_layout(L->tiled_vertex_instances, L->tiled_object_instances, fs);
+    return ws_layout(L->tiled_vertex_instances, L->tiled_object_instances, fs, L->p_frames ? L->n_frames : 0);
 }
 
 // Workspace enough for every valid tuning: every frame on the tiled path, plus the
@@ -341,7 +485,8 @@ static size_t ws_bytes_any(const orrb_layout *L) {
         }
     }
     const FrameScratch fs = frame_scratch(g, nf, v, t, 1024, L->ctx ? L->ctx->n_cu : 256);
-    return ws_layout(L->all_vertex_instances, L->all_object_instances).total + fs.stride * (size_t)fs.grid + 256;
+    return ws_layout(L->all_vertex_instances, L->all_object_instances, FrameScratch(), L->n_frames).total +
+           fs.stride * (size_t)fs.grid + 256;
 }
 
 // Workspace of one render call: the frames' own, then (with spot lights) the shadow
@@ -379,11 +524,12 @@ static void build_items(orrb_layout *L) {
     const int TW = L->tuning.tile_w, TH = L->tuning.tile_h;
     int64_t vi = 0, oi = 0;
     L->gframes = L->gf_verts = L->gf_tris = 0;
+    const int path = L->tuning.path;
+    bool scratch = false;  // path 2 with scenes in global scratch
     for (int64_t f = 0; f < L->n_frames; ++f) {
         FrameInfo &fi = L->frames[f];
         fi.tiles_x = (fi.width + TW - 1) / TW;
         fi.mode = 0;
-        const int path = L->tuning.path;
         if ((path == 0 || path == 2) && L->fits[f] == 1) {
             L->fitems.push_back((int32_t)f);
             fi.vbase = 0;
@@ -391,6 +537,7 @@ static void build_items(orrb_layout *L) {
             continue;
         }
         if (path == 2 && L->fits[f] == 2) {
+            scratch = true;
             L->fitems.push_back((int32_t)f);
             fi.vbase = 0;
             fi.oi_base = 0;
@@ -410,7 +557,10 @@ static void build_items(orrb_layout *L) {
     }
     L->tiled_vertex_instances = vi;
     L->tiled_object_instances = oi;
+    std::vector<int32_t> patched;
+    choose_patches(L, L->fitems, scratch, patched);
     schedule_frames(L);
+    schedule_patches(L, patched);
 }
 
 // Tables of the shading adjoint (independent of the tuning).
@@ -507,6 +657,7 @@ static orrb_status upload_layout(orrb_layout *L) {
     L->o_vitems = P.add(L->vitems);
     L->o_titems = P.add(L->titems);
     L->o_fitems = P.add(L->fitems);
+    L->o_pitems = P.add(L->pitems);
     L->o_light_type = P.add(L->light_type);
     if (L->n_spot > 0) {
         L->o_spot_slot = P.add(L->spot_slot);
@@ -541,6 +692,7 @@ static void fill_args(const orrb_context *ctx, const orrb_layout *L, const orrb_
     a->mesh_pos = (const float4 *)ctx->d_pos.p;
     a->mesh_nrm = (const float4 *)ctx->d_nrm.p;
     a->mesh_tri = (const int4 *)ctx->d_tri.p;
+    a->mesh_box = (const float *)ctx->d_box.p;
     a->mesh_uv = (const float2 *)ctx->d_uv.p;
     a->tex_texels = (const float4 *)ctx->d_texels.p;
     a->tex_info = (const int4 *)ctx->d_tex_info.p;
@@ -673,12 +825,21 @@ orrb_status orrb_add_mesh(orrb_context *ctx, const float *pos, const float *nrm,
     }
     for (int64_t t = 0; t < n_tris; ++t) ctx->tri.push_back(make_int4(idx[3 * t], idx[3 * t + 1], idx[3 * t + 2], 0));
     ctx->uv.resize(ctx->pos.size(), make_float2(0.f, 0.f));
+    const size_t b0 = ctx->mesh_box.size();
+    ctx->mesh_box.insert(ctx->mesh_box.end(), pos, pos + 3);
+    ctx->mesh_box.insert(ctx->mesh_box.end(), pos, pos + 3);
+    for (int64_t k = 0; k < 3 * (int64_t)n_verts; ++k) {
+        ctx->mesh_box[b0 + k % 3] = std::min(ctx->mesh_box[b0 + k % 3], pos[k]);
+        ctx->mesh_box[b0 + 3 + k % 3] = std::max(ctx->mesh_box[b0 + 3 + k % 3], pos[k]);
+    }
     ScopedDevice sd(ctx->device);
-    hipError_t e = ctx->d_pos.upload(ctx->pos.data(), sizeof(float4) * ctx->pos.size());
-    if (e == hipSuccess) e = ctx->d_nrm.upload(ctx->nrm.data(), sizeof(float4) * ctx->nrm.size());
-    if (e == hipSuccess) e = ctx->d_tri.upload(ctx->tri.data(), sizeof(int4) * ctx->tri.size());
-    if (e == hipSuccess) e = ctx->d_uv.upload(ctx->uv.data(), sizeof(float2) * ctx->uv.size());
+    hipError_t e = ctx->d_pos.upload(ctx->pos.data(), sizeof(float4) * ctx->pos.size(), 2 * ctx->d_pos.bytes);
+    if (e == hipSuccess) e = ctx->d_nrm.upload(ctx->nrm.data(), sizeof(float4) * ctx->nrm.size(), 2 * ctx->d_nrm.bytes);
+    if (e == hipSuccess) e = ctx->d_tri.upload(ctx->tri.data(), sizeof(int4) * ctx->tri.size(), 2 * ctx->d_tri.bytes);
+    if (e == hipSuccess) e = ctx->d_uv.upload(ctx->uv.data(), sizeof(float2) * ctx->uv.size(), 2 * ctx->d_uv.bytes);
+    if (e == hipSuccess) e = ctx->d_box.upload(ctx->mesh_box.data(), sizeof(float) * ctx->mesh_box.size(), 2 * ctx->d_box.bytes);
     if (e != hipSuccess) {
+        ctx->mesh_box.resize(b0);
         ctx->pos.resize(v0);
         ctx->nrm.resize(v0);
         ctx->tri.resize(t0);
@@ -814,6 +975,7 @@ orrb_status orrb_layout_create(orrb_context *ctx, const orrb_layout_desc *d, orr
             ob.n_tris = ctx->mesh_tbegin[m + 1] - ctx->mesh_tbegin[m];
             ob.scene_vbase = (int32_t)vb;
             ob.scene_tbase = (int32_t)tb;
+            ob.mesh = m;
             vb += ob.n_verts;
             tb += ob.n_tris;
             if (vb > 0x7fffffff || tb > ORRB_MAX_SCENE_TRIANGLES) {
@@ -857,11 +1019,10 @@ orrb_status orrb_layout_create(orrb_context *ctx, const orrb_layout_desc *d, orr
         fi.light_begin = d->scene_light_begin[s];
         fi.n_lights = d->scene_light_begin[s + 1] - d->scene_light_begin[s];
         fi.track_base = (int32_t)oi;
-        L->fits[f] = frame_fits((int)std::min<int64_t>(L->scene_verts[s], 0x7fffffff), fi.n_obj,
-                                (int)std::min<int64_t>(L->scene_tris[s], 0x7fffffff), fi.width, fi.height)
-                         ? 1
-                     : frame_fits_global(L->scene_verts[s], fi.n_obj, L->scene_tris[s], fi.width, fi.height) ? 2
-                                                                                                              : 0;
+        const bool one = fi.width <= frame_max_side() && fi.height <= frame_max_side();
+        L->fits[f] = frame_fits(L->scene_verts[s], fi.n_obj, L->scene_tris[s])                 ? 1
+                     : one && frame_fits_global(L->scene_verts[s], fi.n_obj, L->scene_tris[s]) ? 2
+                                                                                               : 0;
         fi.mode = 0;
         fi.pad0 = 0;
         pix += (int64_t)fi.width * fi.height;
@@ -954,7 +1115,7 @@ orrb_status orrb_layout_info_get(const orrb_layout *L, orrb_layout_info *info) {
     info->vertex_instances = L->vertex_instances;
     info->triangle_instances = L->triangle_instances;
     info->tile_items = (int64_t)L->titems.size();
-    info->frame_path_frames = L->f_frames;
+    info->frame_path_frames = L->f_frames + L->p_frames;
     info->workspace_bytes = call_ws(L).total;
     info->workspace_bytes_any = ws_bytes_any(L);
     if (L->shadow) info->workspace_bytes_any += call_ws(L, ws_bytes_any(L->shadow)).total - ws_layout(L).total + 256;
@@ -1082,6 +1243,13 @@ orrb_status orrb::render_impl(orrb_context *ctx, const orrb_layout *L, const orr
     a.obj_rot = (float4 *)(ws + w.obj_rot);
     a.obj_bbox = (int4 *)(ws + w.obj_bbox);
     a.queue = (unsigned int *)(ws + w.queue);
+    if (L->p_frames > 0) {
+        a.pitems = L->tab.at<PatchItem>(L->o_pitems);
+        a.n_pitems = (int32_t)L->pitems.size();
+        a.p_side = frame_max_side();
+        frame_limits(&a.p_bin_max, &a.p_surv_max);
+        if (out->stats) a.p_account = (unsigned long long *)(ws + w.account);
+    }
     if (L->gframes > 0) {
         a.fscratch = ws + w.fscratch;
         a.fscratch_stride = (int64_t)w.fs_stride;
@@ -1095,7 +1263,7 @@ orrb_status orrb::render_impl(orrb_context *ctx, const orrb_layout *L, const orr
     hipError_t e = hipSuccess;
     for (int k = 0; k < 3 && e == hipSuccess; ++k) {
         if (k < 2 && a.n_titems == 0) continue;  // no frame on the tiled path
-        if (k == 2 && a.n_fitems == 0) continue;
+        if (k == 2 && a.n_fitems == 0 && a.n_pitems == 0) continue;
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (T.enabled && timing) {
             e0 = T.get();
@@ -1104,6 +1272,7 @@ orrb_status orrb::render_impl(orrb_context *ctx, const orrb_layout *L, const orr
         }
         if (e == hipSuccess)
             e = k == 0 ? launch_vertex(a, st) : k == 1 ? launch_raster(a, st, ctx->n_cu) : launch_frame(a, st, ctx->n_cu);
+        if (k == 2 && e == hipSuccess) e = launch_patch(a, st);
         if (T.enabled && timing && e0 && e1 && e == hipSuccess) {
             e = hipEventRecord(e1, st);
             T.pending[k].push_back({e0, e1});

@@ -1,8 +1,9 @@
 // HIP kernels of the batched randomized renderer, written for CDNA4 (gfx950, wave64).
 //
-// Two paths render a batch; both produce bit-identical outputs because they share
-// every arithmetic primitive below (vertex snapping, edge functions, fragment depth,
-// shading), compiled with floating-point contraction off.
+// Two paths render a batch here (a third, for small batches and large frames, is in
+// orrb_patch.hip); all produce bit-identical outputs because they share every arithmetic
+// primitive (vertex snapping, edge functions, fragment depth, shading), compiled with
+// floating-point contraction off.
 //
 // Frame path (k_frame), for frames whose scene fits in LDS: a persistent kernel, one
 // 1024-thread workgroup per CU rendering frames one after another with no intermediate
@@ -38,25 +39,6 @@
 #include "orrb_post.h"
 
 namespace orrb {
-
-// Light k of frame f's scene (global light l = fi.light_begin + k) in view space, its
-// type word and, for a spot light, its record in spot[] (the index counts the scene's
-// spot lights before it).
-ORRB_INLINE void frame_light(const RenderArgs &a, int f, const FrameInfo &fi, int k, float4 *light, int *ltype,
-                             SpotLight *spot) {
-    const int l = fi.light_begin + k;
-    const float *V = a.view + 12 * (int64_t)f;
-    const int t = a.light_type[l];
-    light[k] = view_light(V, a.light_vec + 3 * (int64_t)l, t == 2 ? 0 : t, a.light_intensity[l]);
-    if (t == 2) {
-        int idx = 0;
-        for (int j = 0; j < k; ++j) idx += a.light_type[fi.light_begin + j] == 2;
-        spot[idx] = spot_setup(a, V, l);
-        ltype[k] = 2 | (idx << 4);
-    } else {
-        ltype[k] = t;
-    }
-}
 
 // ------------------------------------------------------------------------------------
 // tiled path: k_vertex
@@ -162,19 +144,6 @@ struct TileLds {
     int misc[16];  // [0] bin count, [1] next item, [4..8) scan, [8..12) wave counts
 };
 
-// Inclusive sum over the 64 lanes of a wave with DPP: shifts by 1, 2, 4 and 8 inside
-// each 16-lane row, then the last lane of row 0 into row 1 and of row 2 into row 3, then
-// lane 31 into rows 2 and 3 (lanes without a source add 0).
-ORRB_INLINE int wave_scan_add(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
-    return v;
-}
-
 // Exclusive scan over n <= 4 * kBlock counts; writes pre[0..n].
 template <class F>
 ORRB_INLINE void block_scan(F cnt, int n, int *pre, int *wave_tot) {
@@ -237,7 +206,7 @@ ORRB_INLINE void raster_shade_tile(const RenderArgs &a, int item, LD &L) {
 
     for (int p = tid; p < TW * TH; p += kBlock) L.vis[p] = kEmptyKey;
     if (tid == 0) L.misc[0] = 0;
-    if (tid < fi.n_lights) frame_light(a, f, fi, tid, L.light, L.light_type, L.spot);
+    if (tid < fi.n_lights) frame_light(a, f, fi.light_begin, tid, L.light, L.light_type, L.spot);
     __syncthreads();
 
     // ---- visibility: object cull, triangle set-up into the LDS bin, raster ----
@@ -408,20 +377,7 @@ ORRB_INLINE void raster_shade_tile(const RenderArgs &a, int item, LD &L) {
             triv = tri;
         }
         store_pixel(a, po, HW, pix, o, z, segv, triv, key);
-        if (fused) {
-            float n0 = 0.f, n1 = 0.f, n2 = 0.f;
-            if (pq.gi != 0.f) {
-                const unsigned t = grain_texel(a, pq, i, j);
-                n0 = grain_at(pq.g0, t);
-                n1 = grain_at(pq.g1, t);
-                n2 = grain_at(pq.g2, t);
-            }
-            const uchar3 u = post_pixel(pq, o.r0, o.r1, o.r2, n0, n1, n2);
-            uint8_t *d = a.out_rgb8 + 3 * po + pix;
-            d[0] = u.x;
-            d[HW] = u.y;
-            d[2 * HW] = u.z;
-        }
+        if (fused) store_rgb8(a, pq, po, HW, pix, i, j, o);
     }
 
     // ---- tracker: every lane of a wave takes part (the trip count is uniform) ----
@@ -511,7 +467,6 @@ constexpr unsigned kFSpinCap = 1u << 22;  // bound on every wait loop (about 0.3
                                           // the slowest legitimate tile): reached only if a
                                           // peer wave stalls; the kernel then ends with
                                           // unspecified pixels rather than hanging
-constexpr int kInvalidX = (int)0x80000000;
 
 struct BgFrame {
     long long po;  // pixel offset of the frame
@@ -615,13 +570,22 @@ struct FrameLds {
 };
 static_assert(sizeof(FrameLds) <= 160 * 1024, "frame LDS exceeds 160 KB");
 
-bool frame_fits(int n_verts, int n_obj, int n_tris, int width, int height) {
-    // <= 4 x 64 tiles: a tile range packs into 2-bit x and 6-bit y fields
-    return n_verts <= kFVMax && n_obj <= kFOMax && n_tris < 65536 && width <= 4 * kFTileW && height <= 64 * kFTileH;
+bool frame_fits(int64_t n_verts, int n_obj, int64_t n_tris) {
+    return n_verts <= kFVMax && n_obj <= kFOMax && n_tris < 65536;
 }
 
-bool frame_fits_global(int64_t n_verts, int n_obj, int64_t n_tris, int width, int height) {
-    return n_verts <= kFGVMax && n_obj <= kFGOMax && n_tris < 65536 && width <= 4 * kFTileW && height <= 64 * kFTileH;
+bool frame_fits_global(int64_t n_verts, int n_obj, int64_t n_tris) {
+    return n_verts <= kFGVMax && n_obj <= kFGOMax && n_tris < 65536;
+}
+
+int frame_max_side() {  // <= 4 x 64 tiles: a tile range packs into 2-bit x and 6-bit y fields
+    static_assert(4 * kFTileW == 64 * kFTileH, "square limit");
+    return 4 * kFTileW;
+}
+
+void frame_limits(int *bin_max, int *surv_max) {
+    *bin_max = kFBinMax;
+    *surv_max = kFSurvMax;
 }
 
 // Where one frame's scene data live.  G = false: the scene fits in LDS (vertices,
@@ -1323,7 +1287,7 @@ ORRB_INLINE bool frame_render(const RenderArgs &a, FrameLds &S, int item, int se
     }
     if (tid < fi.n_lights) {
         if constexpr (SHADE == 1 || SHADE == 3) {
-            frame_light(a, f, fi, tid, S.light, S.light_type, S.spot);
+            frame_light(a, f, fi.light_begin, tid, S.light, S.light_type, S.spot);
         } else if constexpr (SHADE != 4) {
             const int l = fi.light_begin + tid;
             S.light[tid] = view_light(a.view + 12 * (int64_t)f, a.light_vec + 3 * (int64_t)l, a.light_type[l],

@@ -119,16 +119,6 @@ ORRB_INLINE uchar3 post_pixel(const PostFrame &q, float r, float g, float b, flo
 // with the offset o already in [0, n).
 ORRB_INLINE int grain_coord(int x, int S, int o, int n) { return (x / S + o) % n; }
 
-// x div d for 0 <= x < 2^20 and d >= 1, r = fp32 1 / d: the truncated fp32 product is
-// within one of the quotient (its relative error is below 2^-22, so the absolute
-// error is below 2^-2 for d >= 2; d = 1 gives r = 1 exactly), corrected once each way.
-ORRB_INLINE int div_small(int x, int d, float r) {
-    int k = (int)((float)x * r);
-    k -= k * d > x;
-    k += (k + 1) * d <= x;
-    return k;
-}
-
 // grain_coord for x < 2^19, S and n below 2^19 (so x div S + o < 2^20).
 ORRB_INLINE int grain_coord_small(int x, int S, float rs, int o, int n, float rn) {
     const int t = div_small(x, S, rs) + o;
@@ -177,6 +167,23 @@ ORRB_INLINE void grain_ij(const RenderArgs &a, const PostFrame &q, int i, int j,
 ORRB_INLINE unsigned grain_texel(const RenderArgs &a, const PostFrame &q, int i, int j) {
     const int tx = grain_coord(i, q.gs, q.gx, a.grain_w), ty = grain_coord(j, q.gs, q.gy, a.grain_h);
     return (unsigned)(ty * a.grain_w + tx) * 4u;
+}
+
+// The 8-bit codes of pixel (i, j), linear rgb in o, stored to the three byte planes.
+ORRB_INLINE void store_rgb8(const RenderArgs &a, const PostFrame &q, int64_t po, int64_t HW, int64_t pix, int i, int j,
+                            const PixelOut &o) {
+    float n0 = 0.f, n1 = 0.f, n2 = 0.f;
+    if (q.gi != 0.f) {
+        const unsigned t = grain_texel(a, q, i, j);
+        n0 = grain_at(q.g0, t);
+        n1 = grain_at(q.g1, t);
+        n2 = grain_at(q.g2, t);
+    }
+    const uchar3 u = post_pixel(q, o.r0, o.r1, o.r2, n0, n1, n2);
+    uint8_t *d = a.out_rgb8 + 3 * po + pix;
+    d[0] = u.x;
+    d[HW] = u.y;
+    d[2 * HW] = u.z;
 }
 
 // The 8-bit codes of four consecutive pixels of one row starting at (i, j), linear rgb v

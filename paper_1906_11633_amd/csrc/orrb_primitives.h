@@ -20,6 +20,16 @@ ORRB_INLINE int lanes_below(unsigned long long m) {
     return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
 }
 
+// x div d for 0 <= x < 2^20 and d >= 1, r = fp32 1 / d: the truncated fp32 product is
+// within one of the quotient (its relative error is below 2^-22, so the absolute
+// error is below 2^-2 for d >= 2; d = 1 gives r = 1 exactly), corrected once each way.
+ORRB_INLINE int div_small(int x, int d, float r) {
+    int k = (int)((float)x * r);
+    k -= k * d > x;
+    k += (k + 1) * d <= x;
+    return k;
+}
+
 // floor(a / 256) and ceil(a / 256) for int32 (arithmetic shift floors)
 ORRB_INLINE int floor256(int a) { return a >> 8; }
 ORRB_INLINE int ceil256(int a) { return -((-a) >> 8); }
@@ -34,6 +44,19 @@ ORRB_INLINE int find_slot(const int *base, int n, int x) {  // largest k < n wit
         if (base[mid] <= x) lo = mid; else hi = mid;
     }
     return lo;
+}
+
+// Inclusive sum over the 64 lanes of a wave with DPP: shifts by 1, 2, 4 and 8 inside
+// each 16-lane row, then the last lane of row 0 into row 1 and of row 2 into row 3, then
+// lane 31 into rows 2 and 3 (lanes without a source add 0).
+ORRB_INLINE int wave_scan_add(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return v;
 }
 
 // ------------------------------------------------------------------------------------
@@ -52,6 +75,8 @@ ORRB_INLINE double compose_entry(const float *V, const float *Wp, int e) {
     }
     return fma(v0, (double)Wp[3], fma(v1, (double)Wp[7], fma(v2, (double)Wp[11], v3)));
 }
+
+constexpr int kInvalidX = (int)0x80000000;  // X of an invalid vertex in the LDS paths
 
 struct Snapped {
     int X, Y, valid;
@@ -249,6 +274,25 @@ ORRB_INLINE SpotLight spot_setup(const RenderArgs &a, const float *V, int l) {
     r.cy = K[3];
     r.slot = a.spot_slot[l];
     return r;
+}
+
+// Light k of frame f's scene (whose lights start at light_begin) in view space, its type
+// word and, for a spot light, its record in spot[] (the index counts the scene's spot lights
+// before it).
+ORRB_INLINE void frame_light(const RenderArgs &a, int f, int light_begin, int k, float4 *light, int *ltype,
+                             SpotLight *spot) {
+    const int l = light_begin + k;
+    const float *V = a.view + 12 * (int64_t)f;
+    const int t = a.light_type[l];
+    light[k] = view_light(V, a.light_vec + 3 * (int64_t)l, t == 2 ? 0 : t, a.light_intensity[l]);
+    if (t == 2) {
+        int idx = 0;
+        for (int j = 0; j < k; ++j) idx += a.light_type[light_begin + j] == 2;
+        spot[idx] = spot_setup(a, V, l);
+        ltype[k] = 2 | (idx << 4);
+    } else {
+        ltype[k] = t;
+    }
 }
 
 // Fraction of the 3 x 3 shadow-map texels around view-space point p's texel that see

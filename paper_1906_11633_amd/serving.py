@@ -247,6 +247,10 @@ class Server:
             return
         group, frames, data = [], 0, 0
         free = self.budget - self.used - self.table_bytes
+        if not self.inflight and self.data_bytes(self.queue[0]) > free:
+            # nothing runs whose completion could make room: drop the cached layouts' tables
+            self._evict_except(None)
+            free = self.budget - self.used - self.table_bytes
         while self.queue:
             r = self.queue[0]
             nb = self.data_bytes(r)
