@@ -150,7 +150,10 @@ typedef struct {
  * frame either way.  Frames of scenes that fit in LDS are cut into rectangles for the
  * patch kernel (a workgroup renders one) where that is faster: batches of fewer frames
  * than occupy the chip, a uniform batch's last partly filled round, and frames larger
- * than 256x256.  Other frames go through the tiled path (a vertex kernel, then one
+ * than 256x256.  Frames of larger scenes (<= 127 objects, < 65536 triangles) become
+ * patches after a vertex kernel, under path 2 where that beats the frame kernel's
+ * scratch (batches whose costliest frame outweighs the average work of a CU).  Other
+ * frames go through the tiled path (a vertex kernel, then one
  * workgroup per screen tile). */
 typedef struct {
     int32_t tile_w, tile_h;  /* tiled path: tile size, each in {16, 32, 64} */
@@ -168,8 +171,10 @@ typedef struct {
     int64_t total_pixels;       /* P: depth/seg hold P values, rgb/normal 3P */
     int64_t vertex_instances;   /* sum over frames of the frame's scene vertex count */
     int64_t triangle_instances; /* sum over frames of the frame's scene triangle count */
-    int64_t tile_items;         /* tiled-path work items with the current tuning */
-    int64_t frame_path_frames;  /* frames rendered by the frame or patch kernel with the current tuning */
+    int64_t tile_items;         /* tiled-path work items with the current tuning (under path 0 with the
+                                   patches of scenes beyond LDS) */
+    int64_t frame_path_frames;  /* frames rendered by the frame or patch kernel with the current tuning
+                                   (under path 0: of scenes held in LDS) */
     size_t workspace_bytes;      /* workspace orrb_render_batch needs (current tuning) */
     size_t workspace_bytes_any;  /* workspace enough for every valid tuning */
     size_t grad_workspace_bytes; /* workspace orrb_shade_backward needs */

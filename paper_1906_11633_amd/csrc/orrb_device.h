@@ -41,7 +41,7 @@ struct ObjInfo {
 };
 
 // Work item of k_patch: the pixels [x0, x1) x [y0, y1) of a frame (at most
-// patch_max_pixels() of them); parts: the frame's patches.
+// patch_max_pixels of them); parts: the frame's patches.
 struct PatchItem {
     int32_t frame;
     uint16_t x0, y0, x1, y1;
@@ -174,12 +174,13 @@ hipError_t launch_shadow_cams(const int32_t *spot_light, int n_spot, const float
 hipError_t launch_validate(const RenderArgs &a, const float *post, int n_obj, int n_lights, int n_frames,
                            uint32_t *stats, hipStream_t stream);
 hipError_t read_wait_timeouts(unsigned int *out);  // frame-kernel waits that hit their bound
-hipError_t launch_patch(const RenderArgs &a, hipStream_t stream);
+hipError_t launch_patch(const RenderArgs &a, bool global, hipStream_t stream);
 bool frame_fits(int64_t n_verts, int n_obj, int64_t n_tris);       // scenes held in LDS
 bool frame_fits_global(int64_t n_verts, int n_obj, int64_t n_tris);  // in the frame kernel's scratch
 int frame_max_side();                                                // frames up to this wide and high
 void frame_limits(int *bin_max, int *surv_max);
-int patch_max_pixels();
+int patch_max_pixels(bool global);                       // largest patch (global: scenes not held in LDS)
+bool patch_fits_global(int n_obj, int64_t n_tris);       // such a scene can be rendered as patches
 size_t raster_lds_bytes(int tile_w, int tile_h, int bin_cap);
 // render call shared by orrb_render_batch and orrb_render_batch_noalloc (orrb_host.cpp)
 orrb_status debug_validate(orrb_context *ctx, const orrb_layout *L, const orrb_scenes *sc, const orrb_cameras *cam,

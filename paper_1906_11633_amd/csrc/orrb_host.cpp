@@ -188,19 +188,22 @@ struct orrb_layout {
     std::vector<FrameInfo> frames;
     std::vector<ObjInfo> objs;
     std::vector<int64_t> scene_verts, scene_tris;
-    std::vector<uint8_t> fits;  // per frame: 1 scene fits the frame kernel's LDS, 2 its global scratch, 0 neither
+    // per frame: 1 scene fits in LDS (frame and patch kernel), 2 the frame kernel's global
+    // scratch (and the patch kernel's workspace form), 3 only the latter, 0 none
+    std::vector<uint8_t> fits;
     // frames on the frame kernel with scene data in global scratch (tuning path 2)
     int64_t gframes = 0, gf_verts = 0, gf_tris = 0;
+    int64_t gp_tris = 0;  // most triangles of a larger scene rendered as patches
     std::vector<int2> vitems, titems;
     std::vector<int32_t> fitems;  // frame-kernel schedule (see schedule_frames)
-    std::vector<PatchItem> pitems;  // patches (see schedule_patches)
-    int64_t p_frames = 0;          // frames rendered as patches
+    std::vector<PatchItem> pitems, gpitems;  // patches of LDS-held and of larger scenes (see schedule_patches)
+    int64_t p_frames = 0, gp_frames = 0;     // frames rendered as such patches
     int64_t f_frames = 0;          // frames on the frame kernel
     int32_t f_grid = 0;            // its persistent grid
     int32_t f_dynamic = 0;         // 1: frames claimed from a counter (uneven batch)
     std::vector<int32_t> light_type;
     Packed tab;  // frames, objs, vitems, titems, fitems, pitems, light_type, spot tables
-    size_t o_pitems = 0;
+    size_t o_pitems = 0, o_gpitems = 0;
     size_t o_frames = 0, o_objs = 0, o_vitems = 0, o_titems = 0, o_fitems = 0, o_light_type = 0;
     // spot lights (type 2) with shadow maps: one N x N depth frame per spot light, from
     // its shadow camera, rendered by a sub-layout before the frames themselves
@@ -299,9 +302,9 @@ static bool valid_tuning(const orrb_tuning &t) {
 
 // Estimated work of frame f: triangles (half again when the scene data live in global
 // scratch) plus a quarter per pixel.
-static double frame_cost(const orrb_layout *L, int32_t f) {
+static double frame_cost(const orrb_layout *L, int32_t f, bool scratch) {
     const FrameInfo &fi = L->frames[f];
-    return (double)L->scene_tris[fi.scene] * (fi.mode ? 1.5 : 1.0) + 0.25 * (double)fi.width * fi.height;
+    return (double)L->scene_tris[fi.scene] * (scratch ? 1.5 : 1.0) + 0.25 * (double)fi.width * fi.height;
 }
 
 // Schedule of the frame kernel's persistent grid (min(frames, CUs) workgroups).  A
@@ -320,7 +323,7 @@ static void schedule_frames(orrb_layout *L) {
     std::vector<double> cost(n);
     bool uniform = true;
     for (int64_t k = 0; k < n; ++k) {
-        cost[k] = frame_cost(L, L->fitems[k]);
+        cost[k] = frame_cost(L, L->fitems[k], L->frames[L->fitems[k]].mode != 0);
         uniform = uniform && cost[k] == cost[0];
     }
     if (uniform || n <= L->f_grid) return;
@@ -334,16 +337,16 @@ static void schedule_frames(orrb_layout *L) {
 }
 
 // Cut a frame into patches, a grid of columns (of whole 4-pixel units) and rows whose cells
-// hold at most patch_max_pixels().  More than the least number of patches are asked for
+// hold at most `cap` pixels.  More than the least number of patches are asked for
 // where they all run at once: the frame is cut into `parts` strips of its width (of 256
 // pixels or so of a wider frame), which share out what the middle of the frame shows.
 // Otherwise (batches of several rounds, where the geometry each patch repeats counts) into
 // the least number of columns, in two or more rows where a column would be narrower than 28
 // pixels: hand scenes, 120 frames of 200 x 200, 79 us in 7 columns and 85 us in 7 rows; 48
 // frames of 128 x 128, 33 us in 6 rows, 38 us in 2 x 3 cells.
-static void patch_grid(int W, int H, int parts, int *cols, int *rows) {
+static void patch_grid(int W, int H, int cap, int parts, int *cols, int *rows) {
     constexpr int U = 4;
-    const int nx = (W + U - 1) / U, cap = patch_max_pixels();
+    const int nx = (W + U - 1) / U;
     auto fits = [&](int x, int y) { return (int64_t)U * ((nx + x - 1) / x) * ((H + y - 1) / y) <= cap; };
     int x = 1, y = 1;
     for (y = 1; y <= H; ++y) {
@@ -361,9 +364,9 @@ static void patch_grid(int W, int H, int parts, int *cols, int *rows) {
     *rows = y;
 }
 
-static void cut_frame(const FrameInfo &fi, int32_t f, int parts, std::vector<PatchItem> &out) {
+static void cut_frame(const FrameInfo &fi, int32_t f, int cap, int parts, std::vector<PatchItem> &out) {
     int px, py;
-    patch_grid(fi.width, fi.height, parts, &px, &py);
+    patch_grid(fi.width, fi.height, cap, parts, &px, &py);
     const int nx = (fi.width + 3) / 4;
     for (int y = 0; y < py; ++y)
         for (int x = 0; x < px; ++x) {
@@ -400,9 +403,9 @@ static void choose_patches(const orrb_layout *L, std::vector<int32_t> &frames, b
             patched.push_back(f);
             continue;
         }
-        const double c = frame_cost(L, f);
+        const double c = frame_cost(L, f, false);
         uniform = uniform && (rest.empty() || c == most);
-        sum += c * (fi.width * fi.height <= patch_max_pixels() ? 0.75 : 1.25);
+        sum += c * (fi.width * fi.height <= patch_max_pixels(false) ? 0.75 : 1.25);
         most = std::max(most, c);
         rest.push_back(f);
     }
@@ -422,46 +425,47 @@ static void choose_patches(const orrb_layout *L, std::vector<int32_t> &frames, b
 
 // The patches: enough of them to fill the CUs a little more than once (twice for frames
 // beyond 256 x 256, whose outer patches are often empty), the costlier frames cut into more.
-static void schedule_patches(orrb_layout *L, const std::vector<int32_t> &patched) {
+static void schedule_patches(const orrb_layout *L, const std::vector<int32_t> &patched, bool global,
+                             std::vector<PatchItem> &items) {
     const int64_t n_cu = L->ctx ? L->ctx->n_cu : 256;
-    const int side = frame_max_side();
-    L->pitems.clear();
-    L->p_frames = (int64_t)patched.size();
+    const int side = frame_max_side(), cap = patch_max_pixels(global);
+    items.clear();
     double total = 0.0;
-    for (int32_t f : patched) total += frame_cost(L, f);
+    for (int32_t f : patched) total += frame_cost(L, f, false);
     for (int32_t f : patched) {
         const FrameInfo &fi = L->frames[f];
         const double over = fi.width > side || fi.height > side ? 2.0 : 1.125;
-        cut_frame(fi, f, (int)(over * (double)n_cu * frame_cost(L, f) / total), L->pitems);
+        cut_frame(fi, f, cap, (int)(over * (double)n_cu * frame_cost(L, f, false) / total), items);
     }
     // The middle of a frame usually shows the most: patches nearest to their frame's centre
     // first, so that the last ones to run are light, and the same patch of consecutive
     // frames on consecutive XCDs (in frame order, eight patches a frame put all the middle
     // ones on the same two XCDs: 120 hand frames of 200 x 200 in 8 rows, 136 us against 109).
-    std::vector<double> off(L->pitems.size());
-    std::vector<int32_t> order(L->pitems.size());
+    std::vector<double> off(items.size());
+    std::vector<int32_t> order(items.size());
     for (size_t k = 0; k < off.size(); ++k) {
-        const PatchItem &it = L->pitems[k];
+        const PatchItem &it = items[k];
         const FrameInfo &fi = L->frames[it.frame];
         off[k] = std::max(std::fabs((it.x0 + it.x1) / (double)fi.width - 1.0), std::fabs((it.y0 + it.y1) / (double)fi.height - 1.0));
         order[k] = (int32_t)k;
     }
     std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return off[x] < off[y]; });
-    std::vector<PatchItem> sorted(L->pitems.size());
-    for (size_t k = 0; k < order.size(); ++k) sorted[k] = L->pitems[order[k]];
-    L->pitems.swap(sorted);
+    std::vector<PatchItem> sorted(items.size());
+    for (size_t k = 0; k < order.size(); ++k) sorted[k] = items[order[k]];
+    items.swap(sorted);
 }
 
 // Kernel launches of one render call: the shadow frames' (camera gather + their own),
-// vertex + raster for the tiled path, the frame kernel (after a counter clear when its
+// vertex for the tiled path and larger scenes' patches, raster for the tiled path, the frame kernel (after a counter clear when its
 // frames are claimed at run time), the patch kernel (with counters or Tracker records a call
 // launches one more before it).
 static int64_t render_kernels(const orrb_layout *L) {
     if (L->n_frames == 0) return 0;
     int64_t n = L->shadow ? 1 + render_kernels(L->shadow) : 0;
-    if (!L->titems.empty()) n += 2;
+    if (!L->vitems.empty() || !L->titems.empty()) n += 1;
+    if (!L->titems.empty()) n += 1;
     if (!L->fitems.empty()) n += 1 + L->f_dynamic;
-    if (!L->pitems.empty()) n += 1;
+    n += !L->pitems.empty() + !L->gpitems.empty();
     return n;
 }
 
@@ -469,7 +473,7 @@ static WsLayout ws_layout(const orrb_layout *L) {
     const FrameScratch fs =
         frame_scratch(L->gframes, L->f_frames, L->gf_verts, L->gf_tris, L->tuning.bin_cap,
                       L->ctx ? L->ctx->n_cu : 256);
-    return ws_layout(L->tiled_vertex_instances, L->tiled_object_instances, fs, L->p_frames ? L->n_frames : 0);
+    return ws_layout(L->tiled_vertex_instances, L->tiled_object_instances, fs, L->p_frames + L->gp_frames ? L->n_frames : 0);
 }
 
 // Workspace enough for every valid tuning: every frame on the tiled path, plus the
@@ -477,7 +481,7 @@ static WsLayout ws_layout(const orrb_layout *L) {
 static size_t ws_bytes_any(const orrb_layout *L) {
     int64_t g = 0, v = 0, t = 0, nf = 0;
     for (int64_t f = 0; f < L->n_frames; ++f) {
-        nf += L->fits[f] != 0;
+        nf += L->fits[f] == 1 || L->fits[f] == 2;
         if (L->fits[f] == 2) {
             ++g;
             v = std::max<int64_t>(v, L->scene_verts[L->frames[f].scene]);
@@ -512,35 +516,51 @@ static CallWs call_ws(const orrb_layout *L, size_t shadow_ws_bytes) {
 }
 static CallWs call_ws(const orrb_layout *L) { return call_ws(L, L->shadow ? ws_layout(L->shadow).total : 0); }
 
-// Split frames between the frame kernel and the tiled path and build the work items.
-// Path 0: the frame kernel takes frames whose scene fits in LDS; path 1: every frame
-// on the tiled path; path 2: the frame kernel also takes larger scenes (up to 65,536
-// vertices, 127 objects, 65,535 triangles, 256 x 256 pixels) with their data in global
-// scratch, so an uneven batch of such frames is one launch.
+// Path 2, scenes beyond LDS: whether the frame kernel renders them from global scratch (or
+// they become patches).  The frame kernel takes as long as its costliest frame or, with many
+// frames, as the work over the CUs; the patches cost about 1.3 times as much work (and a
+// vertex kernel) but spread over the chip.  Measured (one MI355X, us, frame kernel / patches):
+// 24 uneven frames 175 / 54, 192: 365 / 172, 384: 382 / 273, 768 (work over the CUs equal to
+// the costliest frame): 514 / 516, 1,536: 713 / 890, 3,072: 1,399 / 1,694.
+static bool frame_scratch_pays(const orrb_layout *L) {
+    double sum = 0.0, most = 0.0;
+    for (int32_t f = 0; f < (int32_t)L->n_frames; ++f) {
+        if (L->fits[f] != 1 && L->fits[f] != 2) continue;
+        const double c = frame_cost(L, f, L->fits[f] == 2);
+        sum += c;
+        most = std::max(most, c);
+    }
+    return sum >= (L->ctx ? L->ctx->n_cu : 256) * most;
+}
+
+// Split frames between the frame kernel, patches and the tiled path and build the work
+// items.  Path 0: frames whose scene fits in LDS go to the frame kernel or become patches
+// (choose_patches), larger scenes (up to 127 objects, 65,535 triangles) become patches
+// after k_vertex; path 1: every frame on the tiled path; path 2: the frame kernel also takes
+// larger scenes (up to 65,536 vertices, 127 objects, 65,535 triangles, 256 x 256 pixels) with
+// their data in global scratch where that pays, so a large uneven batch is one launch.
 static void build_items(orrb_layout *L) {
     L->titems.clear();
     L->vitems.clear();
     L->fitems.clear();
     const int TW = L->tuning.tile_w, TH = L->tuning.tile_h;
     int64_t vi = 0, oi = 0;
-    L->gframes = L->gf_verts = L->gf_tris = 0;
+    L->gframes = L->gf_verts = L->gf_tris = L->gp_tris = 0;
     const int path = L->tuning.path;
-    bool scratch = false;  // path 2 with scenes in global scratch
+    const bool scratch = path == 2 && frame_scratch_pays(L);
+    std::vector<int32_t> patched, gpatched;
     for (int64_t f = 0; f < L->n_frames; ++f) {
         FrameInfo &fi = L->frames[f];
         fi.tiles_x = (fi.width + TW - 1) / TW;
         fi.mode = 0;
-        if ((path == 0 || path == 2) && L->fits[f] == 1) {
+        fi.vbase = 0;
+        fi.oi_base = 0;
+        if (path != 1 && L->fits[f] == 1) {
             L->fitems.push_back((int32_t)f);
-            fi.vbase = 0;
-            fi.oi_base = 0;
             continue;
         }
-        if (path == 2 && L->fits[f] == 2) {
-            scratch = true;
+        if (scratch && L->fits[f] == 2) {
             L->fitems.push_back((int32_t)f);
-            fi.vbase = 0;
-            fi.oi_base = 0;
             fi.mode = 1;
             L->gframes++;
             L->gf_verts = std::max<int64_t>(L->gf_verts, L->scene_verts[fi.scene]);
@@ -552,15 +572,22 @@ static void build_items(orrb_layout *L) {
         for (int k = 0; k < fi.n_obj; ++k) L->vitems.push_back(make_int2((int)f, k));
         vi += L->scene_verts[fi.scene];
         oi += fi.n_obj;
+        if (path != 1 && L->fits[f] != 0) {
+            gpatched.push_back((int32_t)f);
+            L->gp_tris = std::max<int64_t>(L->gp_tris, L->scene_tris[fi.scene]);
+            continue;
+        }
         const int ty = (fi.height + TH - 1) / TH;
         for (int t = 0; t < fi.tiles_x * ty; ++t) L->titems.push_back(make_int2((int)f, t));
     }
     L->tiled_vertex_instances = vi;
     L->tiled_object_instances = oi;
-    std::vector<int32_t> patched;
-    choose_patches(L, L->fitems, scratch, patched);
+    choose_patches(L, L->fitems, L->gframes > 0, patched);
     schedule_frames(L);
-    schedule_patches(L, patched);
+    schedule_patches(L, patched, false, L->pitems);
+    schedule_patches(L, gpatched, true, L->gpitems);
+    L->p_frames = (int64_t)patched.size();
+    L->gp_frames = (int64_t)gpatched.size();
 }
 
 // Tables of the shading adjoint (independent of the tuning).
@@ -658,6 +685,7 @@ static orrb_status upload_layout(orrb_layout *L) {
     L->o_titems = P.add(L->titems);
     L->o_fitems = P.add(L->fitems);
     L->o_pitems = P.add(L->pitems);
+    L->o_gpitems = P.add(L->gpitems);
     L->o_light_type = P.add(L->light_type);
     if (L->n_spot > 0) {
         L->o_spot_slot = P.add(L->spot_slot);
@@ -1022,6 +1050,7 @@ orrb_status orrb_layout_create(orrb_context *ctx, const orrb_layout_desc *d, orr
         const bool one = fi.width <= frame_max_side() && fi.height <= frame_max_side();
         L->fits[f] = frame_fits(L->scene_verts[s], fi.n_obj, L->scene_tris[s])                 ? 1
                      : one && frame_fits_global(L->scene_verts[s], fi.n_obj, L->scene_tris[s]) ? 2
+                     : patch_fits_global(fi.n_obj, L->scene_tris[s])                           ? 3
                                                                                                : 0;
         fi.mode = 0;
         fi.pad0 = 0;
@@ -1114,8 +1143,10 @@ orrb_status orrb_layout_info_get(const orrb_layout *L, orrb_layout_info *info) {
     info->total_pixels = L->total_pixels;
     info->vertex_instances = L->vertex_instances;
     info->triangle_instances = L->triangle_instances;
-    info->tile_items = (int64_t)L->titems.size();
-    info->frame_path_frames = L->f_frames + L->p_frames;
+    // larger scenes' patches count as the tiled path's under path 0, as the frame path's under 2
+    const bool gp_tiled = L->tuning.path != 2;
+    info->tile_items = (int64_t)(L->titems.size() + (gp_tiled ? L->gpitems.size() : 0));
+    info->frame_path_frames = L->f_frames + L->p_frames + (gp_tiled ? 0 : L->gp_frames);
     info->workspace_bytes = call_ws(L).total;
     info->workspace_bytes_any = ws_bytes_any(L);
     if (L->shadow) info->workspace_bytes_any += call_ws(L, ws_bytes_any(L->shadow)).total - ws_layout(L).total + 256;
@@ -1243,13 +1274,6 @@ orrb_status orrb::render_impl(orrb_context *ctx, const orrb_layout *L, const orr
     a.obj_rot = (float4 *)(ws + w.obj_rot);
     a.obj_bbox = (int4 *)(ws + w.obj_bbox);
     a.queue = (unsigned int *)(ws + w.queue);
-    if (L->p_frames > 0) {
-        a.pitems = L->tab.at<PatchItem>(L->o_pitems);
-        a.n_pitems = (int32_t)L->pitems.size();
-        a.p_side = frame_max_side();
-        frame_limits(&a.p_bin_max, &a.p_surv_max);
-        if (out->stats) a.p_account = (unsigned long long *)(ws + w.account);
-    }
     if (L->gframes > 0) {
         a.fscratch = ws + w.fscratch;
         a.fscratch_stride = (int64_t)w.fs_stride;
@@ -1262,8 +1286,9 @@ orrb_status orrb::render_impl(orrb_context *ctx, const orrb_layout *L, const orr
     KernelTimer &T = ctx->timer;
     hipError_t e = hipSuccess;
     for (int k = 0; k < 3 && e == hipSuccess; ++k) {
-        if (k < 2 && a.n_titems == 0) continue;  // no frame on the tiled path
-        if (k == 2 && a.n_fitems == 0 && a.n_pitems == 0) continue;
+        if (k == 0 && a.n_titems == 0 && a.n_vitems == 0) continue;  // no frame needs k_vertex
+        if (k == 1 && a.n_titems == 0) continue;
+        if (k == 2 && a.n_fitems == 0 && L->pitems.empty() && L->gpitems.empty()) continue;
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (T.enabled && timing) {
             e0 = T.get();
@@ -1272,7 +1297,21 @@ orrb_status orrb::render_impl(orrb_context *ctx, const orrb_layout *L, const orr
         }
         if (e == hipSuccess)
             e = k == 0 ? launch_vertex(a, st) : k == 1 ? launch_raster(a, st, ctx->n_cu) : launch_frame(a, st, ctx->n_cu);
-        if (k == 2 && e == hipSuccess) e = launch_patch(a, st);
+        for (int g = 0; k == 2 && g < 2 && e == hipSuccess; ++g) {  // patches of LDS-held, then of larger scenes
+            const std::vector<PatchItem> &items = g ? L->gpitems : L->pitems;
+            RenderArgs b = a;
+            b.pitems = L->tab.at<PatchItem>(g ? L->o_gpitems : L->o_pitems);
+            b.n_pitems = (int32_t)items.size();
+            b.p_side = frame_max_side();
+            frame_limits(&b.p_bin_max, &b.p_surv_max);
+            if (g) {  // the frame kernel's global scratch (path 2) would have had these limits
+                const FrameScratch fs = frame_scratch(1, 1, 1, L->gp_tris, L->tuning.bin_cap, 1);
+                b.p_bin_max = (int32_t)std::min<int64_t>(fs.bins, 0x7fffffff);
+                b.p_surv_max = (int32_t)fs.surv;
+            }
+            if (out->stats && (!g || L->tuning.path == 2)) b.p_account = (unsigned long long *)(ws + w.account);
+            e = launch_patch(b, g != 0, st);
+        }
         if (T.enabled && timing && e0 && e1 && e == hipSuccess) {
             e = hipEventRecord(e1, st);
             T.pending[k].push_back({e0, e1});

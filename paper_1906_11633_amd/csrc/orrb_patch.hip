@@ -1,8 +1,10 @@
 // Patch path (k_patch): rectangles of frames, for batches with too few frames to occupy the
 // chip with one workgroup per frame and for frames larger than the frame kernel takes.
 //
-// One 1024-thread workgroup renders one patch of at most kPPixels pixels whose scene fits
-// in LDS (the frame kernel's limits), with no intermediate data in global memory:
+// One 1024-thread workgroup renders one patch.  Scenes that fit in LDS (the frame kernel's
+// limits) need no intermediate data in global memory; for larger ones (G) k_vertex has put
+// the snapped vertices and the objects' pixel ranges in the workspace, steps 1 and 2 fall
+// away, and the patch may be larger:
 //   1. eight lanes per object project its mesh's bounding box; objects that miss the patch
 //      are left out;
 //   2. the kept objects' vertices are transformed and snapped (FP64) into LDS, 64 vertices
@@ -26,7 +28,8 @@
 // the other 63 waiting (8 to 12 measured alike, 32 up to 15 % slower).
 // One MI355X, us a call, one workgroup per frame before / patches: 4 plain 64 x 64 frames
 // 27 / 9.5, 6 hand frames of 128 x 128 68 / 16, 48 of 200 x 200 118 / 49; 2 of 1024 x 768
-// (tiled path before) 113 / 30.
+// (tiled path before) 113 / 30.  Larger scenes (G), 24 / 192 / 384 uneven frames: tiled path
+// 132 / 387 / 683, frame kernel with global scratch 175 / 365 / 382, patches 54 / 172 / 276.
 #include "orrb_post.h"
 
 namespace orrb {
@@ -36,29 +39,51 @@ constexpr int kPW = kPT / kWave;     // waves
 constexpr int kPVMax = 6976;         // scene vertices held in LDS (the frame kernel's limit)
 constexpr int kPOMax = 48;           // scene objects (likewise; one lane each)
 constexpr int kPPixels = 6784;       // pixels of a patch
+constexpr int kPGOMax = 127;         // objects of a larger scene
+constexpr int kPGPixels = 16384;     // pixels of its patches
 constexpr int kPOwn = 10;            // most pixels (of its range) of a triangle that one lane rasterizes
 constexpr int kPBig = 1024;          // larger triangles queued (beyond: one lane's work as well)
 
+template <bool G>
 struct PatchLds {
-    int2 XY[kPVMax];
-    float iw[kPVMax];
-    unsigned long long vis[kPPixels];  // (depth bits << 32) | object << 16 | scene triangle
-    double M[kPOMax][12];
-    float R[kPOMax][9];
-    Material mat[kPOMax];
-    int tbase[kPOMax], mtb[kPOMax], mvb[kPOMax], vbase[kPOMax], seg[kPOMax];
+    static constexpr int kObj = G ? kPGOMax : kPOMax;
+    // G = false: the kept objects' snapped vertices, all objects' matrices
+    int2 XY[G ? 1 : kPVMax];
+    float iw[G ? 1 : kPVMax];
+    double M[G ? 1 : kPOMax][12];
+    unsigned char keep[G ? 1 : kPOMax];
+    unsigned long long vis[G ? kPGPixels : kPPixels];  // (depth bits << 32) | object << 16 | scene triangle
+    float R[kObj][9];
+    Material mat[kObj];
+    int tbase[kObj], mtb[kObj], mvb[kObj], vbase[kObj], seg[kObj];
     float4 light[kMaxLights];
     int ltype[kMaxLights];
     SpotLight spot[kMaxSpots];
-    unsigned char keep[kPOMax];
     unsigned small[kPW][2 * kWave];  // per wave: visible small triangles, object << 16 | triangle
     unsigned big[kPBig];             // queued larger ones
     int n_big, next_big;
     unsigned account[2];  // bin entries and survivors the frame kernel would count
 };
-static_assert(sizeof(PatchLds) <= 160 * 1024, "patch LDS exceeds 160 KB");
+static_assert(sizeof(PatchLds<false>) <= 160 * 1024 && sizeof(PatchLds<true>) <= 160 * 1024, "patch LDS exceeds 160 KB");
 
-int patch_max_pixels() { return kPPixels; }
+int patch_max_pixels(bool global) { return global ? kPGPixels : kPPixels; }
+bool patch_fits_global(int n_obj, int64_t n_tris) { return n_obj <= kPGOMax && n_tris < 65536; }
+
+// The snapped vertices of the frame: in LDS, or k_vertex's records (X, Y, bits of 1 / w,
+// valid) in the workspace.
+template <bool G>
+struct PatchVerts {
+    const PatchLds<G> &S;
+    const int4 *records;
+    ORRB_INLINE int4 get(int v) const {
+        if constexpr (G) {
+            return records[v];
+        } else {
+            const int2 p = S.XY[v];
+            return make_int4(p.x, p.y, __float_as_int(S.iw[v]), p.x != kInvalidX);
+        }
+    }
+};
 
 // Objects of the patch: keep[k] = 1 where scene object k may touch its pixels.  Eight lanes
 // per object project the corners of its mesh's bounding box (FP64, any affine pose).  When
@@ -68,7 +93,7 @@ int patch_max_pixels() { return kPPixels; }
 // widened by a pixel for rounding, misses the patch.  Otherwise it is kept: objects left out
 // have no vertex that the call's counters would count.  Also leaves the objects' matrices
 // in M and R.
-ORRB_INLINE void patch_cull(const RenderArgs &a, PatchLds &S, const PatchItem &it, const FrameInfo &fi, int tid) {
+ORRB_INLINE void patch_cull(const RenderArgs &a, PatchLds<false> &S, const PatchItem &it, const FrameInfo &fi, int tid) {
     const int k = tid >> 3, c = tid & 7;
     if (tid - lane_id() >= 8 * fi.n_obj) return;  // wave-uniform
     const float *V = a.view + 12 * (int64_t)it.frame, *K = a.intr + 4 * (int64_t)it.frame;
@@ -136,13 +161,13 @@ struct PatchTri {
     int flags, id;               // edge flags (tri_flags); object << 16 | scene triangle
 };
 
-ORRB_INLINE void patch_pixel(PatchLds &S, const PatchTri &t, const Edges &e, int cell) {
-    atomicMin(&S.vis[cell], vis_key(fragment_depth(e, t.iwa, t.iwb, t.iwc, t.area), t.id));
+ORRB_INLINE void patch_pixel(unsigned long long *vis, const PatchTri &t, const Edges &e, int cell) {
+    atomicMin(&vis[cell], vis_key(fragment_depth(e, t.iwa, t.iwb, t.iwc, t.area), t.id));
 }
 
 // Rasterize the pixels (i0 + sc + m step, j0 + sr + n step) of the triangle's range, step =
 // 1 << shift.  Integer edge functions are stepped (the same integers as evaluated ones).
-ORRB_INLINE void patch_raster(PatchLds &S, const PatchTri &t, int x0, int y0, int pw, int sc, int sr, int shift) {
+ORRB_INLINE void patch_raster(unsigned long long *vis, const PatchTri &t, int x0, int y0, int pw, int sc, int sr, int shift) {
     const int step = 1 << shift;
     if (!(t.flags & 8)) {
         const int b0 = (t.flags & 1) ? 0 : 1, b1 = (t.flags & 2) ? 0 : 1, b2 = (t.flags & 4) ? 0 : 1;
@@ -158,7 +183,7 @@ ORRB_INLINE void patch_raster(PatchLds &S, const PatchTri &t, int x0, int y0, in
                     ed.e0 = (float)e0;
                     ed.e1 = (float)e1;
                     ed.e2 = (float)e2;
-                    patch_pixel(S, t, ed, row + ii);
+                    patch_pixel(vis, t, ed, row + ii);
                 }
                 e0 += es.dx0;
                 e1 += es.dx1;
@@ -172,19 +197,18 @@ ORRB_INLINE void patch_raster(PatchLds &S, const PatchTri &t, int x0, int y0, in
         for (int jj = t.j0 + sr; jj <= t.j1; jj += step)
             for (int ii = t.i0 + sc; ii <= t.i1; ii += step) {
                 const Edges e = edge_eval(t.xa, t.ya, t.xb, t.yb, t.xc, t.yc, (ii << 8) + 128, (jj << 8) + 128, t.flags);
-                if (e.covered) patch_pixel(S, t, e, (jj - y0) * pw + (ii - x0));
+                if (e.covered) patch_pixel(vis, t, e, (jj - y0) * pw + (ii - x0));
             }
     }
 }
 
-// Set-up of the triangle with LDS vertices ia, ib, ic (positive-area order of a front
-// face), clipped to the patch: its pixels' number, 0 if it is invalid, a back face or
-// misses the patch.  (The 1 / w and the edge flags are only set when it is not.)
-ORRB_INLINE int patch_setup(const PatchLds &S, int ia, int ib, int ic, int px0, int py0, int pw, int ph, PatchTri &T) {
-    const int2 A = S.XY[ia], B = S.XY[ib], C = S.XY[ic];
+// Set-up of the triangle with snapped vertices A, B, C (PatchVerts; positive-area order of a
+// front face), clipped to the patch: its pixels' number, 0 if it is invalid, a back face or
+// misses the patch.
+ORRB_INLINE int patch_setup(int4 A, int4 B, int4 C, int px0, int py0, int pw, int ph, PatchTri &T) {
+    if (!(A.w & B.w & C.w)) return 0;
     const int xmin = min(A.x, min(B.x, C.x)), xmax = max(A.x, max(B.x, C.x));
     const int ymin = min(A.y, min(B.y, C.y)), ymax = max(A.y, max(B.y, C.y));
-    if (xmin == kInvalidX) return 0;  // the least int: a triangle with an invalid vertex
     T.i0 = max(ceil256(xmin - 128), px0);
     T.i1 = min(floor256(xmax - 128), px0 + pw - 1);
     T.j0 = max(ceil256(ymin - 128), py0);
@@ -198,9 +222,9 @@ ORRB_INLINE int patch_setup(const PatchLds &S, int ia, int ib, int ic, int px0, 
     T.area = (float)area;
     T.flags = top_left(C.x - B.x, C.y - B.y) | (top_left(A.x - C.x, A.y - C.y) << 1) |
               (top_left(B.x - A.x, B.y - A.y) << 2) | (large ? 8 : 0);
-    T.iwa = S.iw[ia];
-    T.iwb = S.iw[ib];
-    T.iwc = S.iw[ic];
+    T.iwa = __int_as_float(A.z);
+    T.iwb = __int_as_float(B.z);
+    T.iwc = __int_as_float(C.z);
     return (T.i1 - T.i0 + 1) * (T.j1 - T.j0 + 1);
 }
 
@@ -217,9 +241,9 @@ ORRB_INLINE void patch_account(const RenderArgs &a, const PatchItem &it, unsigne
     stat_add(a, ORRB_STAT_SURVIVOR_RESETUP, !overflow && ((sum >> 32) & 0xfffff) > (unsigned)a.p_surv_max ? 1u : 0u);
 }
 
-template <bool AUX, int SHADE>
+template <bool AUX, bool G, int SHADE>
 __global__ __launch_bounds__(kPT) void k_patch(RenderArgs a) {
-    __shared__ PatchLds S;
+    __shared__ PatchLds<G> S;
     const PatchItem it = a.pitems[blockIdx.x];
     const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid) / kWave;
     const int f = it.frame;
@@ -228,7 +252,8 @@ __global__ __launch_bounds__(kPT) void k_patch(RenderArgs a) {
     const int px0 = it.x0, py0 = it.y0, pw = it.x1 - it.x0, ph = it.y1 - it.y0, n_pix = pw * ph;
 
     // ---- 1: objects, lights, tables ----
-    patch_cull(a, S, it, fi, tid);
+    const PatchVerts<G> verts{S, G ? a.vtx_pos + fi.vbase : nullptr};
+    if constexpr (!G) patch_cull(a, S, it, fi, tid);
     if (wave == kPW - 1) {
         if (lane < fi.n_lights) {
             if constexpr (SHADE == 1 || SHADE == 3) {
@@ -243,9 +268,9 @@ __global__ __launch_bounds__(kPT) void k_patch(RenderArgs a) {
         if (lane < 2) S.account[lane] = 0u;
         if (lane == 2) S.n_big = S.next_big = 0;
     }
-    // lane k of every wave: scene object k
+    // lane k of every wave: scene object k (G: of the current 64 objects)
     int nv = 0, nt = 0, mvb = 0, mtb = 0, tbase = 0;
-    if (lane < n_obj) {
+    if (!G && lane < n_obj) {
         const ObjInfo &ob = a.objs[fi.obj_begin + lane];
         nv = ob.n_verts;
         nt = ob.n_tris;
@@ -253,7 +278,25 @@ __global__ __launch_bounds__(kPT) void k_patch(RenderArgs a) {
         mtb = ob.mesh_tbegin;
         tbase = ob.scene_tbase;
     }
-    if (wave == kPW - 2 && lane < n_obj) {
+    if constexpr (G) {
+        if (tid < n_obj) {
+            const int o = fi.obj_begin + tid;
+            const ObjInfo &ob = a.objs[o];
+            S.tbase[tid] = ob.scene_tbase;
+            S.mtb[tid] = ob.mesh_tbegin;
+            S.mvb[tid] = ob.mesh_vbegin;
+            S.vbase[tid] = ob.scene_vbase;
+            S.seg[tid] = a.seg[o];
+            S.mat[tid] = object_material(a, o);
+        }
+        for (int e = tid; e < 3 * n_obj; e += kPT) {
+            const float4 r = a.obj_rot[3 * (int64_t)fi.oi_base + e];
+            float *R = S.R[e / 3] + 3 * (e % 3);
+            R[0] = r.x;
+            R[1] = r.y;
+            R[2] = r.z;
+        }
+    } else if (wave == kPW - 2 && lane < n_obj) {
         const int o = fi.obj_begin + lane;
         S.tbase[lane] = tbase;
         S.mtb[lane] = mtb;
@@ -266,15 +309,22 @@ __global__ __launch_bounds__(kPT) void k_patch(RenderArgs a) {
     __syncthreads();
 
     // the kept objects' work lists: 64 vertices, or 64 triangles, of one object per unit
-    const bool keep = lane < n_obj && S.keep[lane] != 0;
-    const int vu = keep ? (nv + kWave - 1) / kWave : 0, tu = keep ? (nt + kWave - 1) / kWave : 0;
-    const int vi = wave_scan_add(vu), ti = wave_scan_add(tu), vb = wave_scan_add(keep ? nv : 0) - nv;
-    const int v_units = __builtin_amdgcn_readlane(vi, kWave - 1), t_units = __builtin_amdgcn_readlane(ti, kWave - 1);
-    const int vfirst = vi - vu, tfirst = ti - tu;
-    if (wave == 0 && keep) S.vbase[lane] = vb;
+    int tu = 0, tfirst = 0, t_units = 0, vb = 0;
+    if constexpr (!G) {
+        const bool keep = lane < n_obj && S.keep[lane] != 0;
+        tu = keep ? (nt + kWave - 1) / kWave : 0;
+        const int ti = wave_scan_add(tu);
+        tfirst = ti - tu;
+        t_units = __builtin_amdgcn_readlane(ti, kWave - 1);
+        vb = wave_scan_add(keep ? nv : 0) - nv;
+        if (wave == 0 && keep) S.vbase[lane] = vb;
+    }
 
     // ---- 2: vertices (the next unit's positions are loaded before this one's are used) ----
-    {
+    if constexpr (!G) {
+        const bool keep = tu > 0;
+        const int vu = keep ? (nv + kWave - 1) / kWave : 0, vi = wave_scan_add(vu), vfirst = vi - vu;
+        const int v_units = __builtin_amdgcn_readlane(vi, kWave - 1);
         const float *K = a.intr + 4 * (int64_t)f;
         const double fx = K[0], fy = K[1], cx = K[2], cy = K[3], nearp = a.near_plane[f];
         unsigned n_near = 0, n_guard = 0;
@@ -320,8 +370,10 @@ __global__ __launch_bounds__(kPT) void k_patch(RenderArgs a) {
         if (tn >= __builtin_amdgcn_readlane(nt, kn)) tn = -1;
         else trn = a.mesh_tri[__builtin_amdgcn_readlane(mtb, kn) + tn];
     };
-    if (wave < t_units) tfetch(wave);
-    __syncthreads();
+    if constexpr (!G) {
+        if (wave < t_units) tfetch(wave);
+        __syncthreads();
+    }
 
     // ---- 3: triangles ----
     // entry q of a list of n: set up (again) and rasterize, by (sc, sr, shift) of patch_raster
@@ -333,9 +385,10 @@ __global__ __launch_bounds__(kPT) void k_patch(RenderArgs a) {
             const int k = (int)(e >> 16), t = (int)(e & 0xffffu), base = S.vbase[k];
             const int4 tri = a.mesh_tri[S.mtb[k] + t];
             PatchTri T;
-            if (patch_setup(S, base + tri.x, base + tri.z, base + tri.y, px0, py0, pw, ph, T) > 0) {
+            if (patch_setup(verts.get(base + tri.x), verts.get(base + tri.z), verts.get(base + tri.y), px0, py0, pw, ph,
+                            T) > 0) {
                 T.id = (k << 16) | (S.tbase[k] + t);
-                patch_raster(S, T, px0, py0, pw, sc, sr, shift);
+                patch_raster(S.vis, T, px0, py0, pw, sc, sr, shift);
             }
         }
         __builtin_amdgcn_wave_barrier();
@@ -343,43 +396,63 @@ __global__ __launch_bounds__(kPT) void k_patch(RenderArgs a) {
     unsigned *buf = S.small[wave];
     int n_buf = 0;
     unsigned entries = 0, survivors = 0;
-    for (int u = wave; u < t_units; u += kPW) {
-        const int k = kn, t = tn;
-        const int4 tri = trn;
-        if (u + kPW < t_units) tfetch(u + kPW);
-        const int base = __builtin_amdgcn_readlane(vb, k);
-        PatchTri T;
-        const int n = t >= 0 ? patch_setup(S, base + tri.x, base + tri.z, base + tri.y, px0, py0, pw, ph, T) : 0;
-        if (a.p_account && n > 0 && fi.width <= a.p_side && fi.height <= a.p_side) {
-            const int xmin = min(T.xa, min(T.xb, T.xc)), xmax = max(T.xa, max(T.xb, T.xc));
-            const int ymin = min(T.ya, min(T.yb, T.yc)), ymax = max(T.ya, max(T.yb, T.yc));
-            const int i0 = max(ceil256(xmin - 128), 0), j0 = max(ceil256(ymin - 128), 0);
-            if (i0 >= px0 && j0 >= py0) {  // its first pixel lies here
-                const int i1 = min(floor256(xmax - 128), fi.width - 1), j1 = min(floor256(ymax - 128), fi.height - 1);
-                entries += (unsigned)((i1 / 64 - i0 / 64 + 1) * (j1 / 4 - j0 / 4 + 1));
-                ++survivors;
+    int group = 0;  // first of the lanes' objects
+    do {
+        if constexpr (G) {
+            const bool in = group + lane < n_obj;
+            const ObjInfo &ob = a.objs[fi.obj_begin + (in ? group + lane : 0)];
+            const int4 bb = in ? a.obj_bbox[fi.oi_base + group + lane] : make_int4(1, 1, 0, 0);
+            const bool keep = bb.x <= bb.z && bb.y <= bb.w && bb.z >= px0 && bb.x < px0 + pw && bb.w >= py0 && bb.y < py0 + ph;
+            nt = ob.n_tris;
+            mtb = ob.mesh_tbegin;
+            vb = ob.scene_vbase;
+            tu = keep ? (nt + kWave - 1) / kWave : 0;
+            const int ti = wave_scan_add(tu);
+            tfirst = ti - tu;
+            t_units = __builtin_amdgcn_readlane(ti, kWave - 1);
+            if (wave < t_units) tfetch(wave);
+        }
+        for (int u = wave; u < t_units; u += kPW) {
+            const int k = kn, t = tn;
+            const int4 tri = trn;
+            if (u + kPW < t_units) tfetch(u + kPW);
+            const int base = __builtin_amdgcn_readlane(vb, k);
+            PatchTri T;
+            const int n = t >= 0 ? patch_setup(verts.get(base + tri.x), verts.get(base + tri.z), verts.get(base + tri.y),
+                                               px0, py0, pw, ph, T)
+                                 : 0;
+            if (a.p_account && n > 0 && fi.width <= a.p_side && fi.height <= a.p_side) {
+                const int xmin = min(T.xa, min(T.xb, T.xc)), xmax = max(T.xa, max(T.xb, T.xc));
+                const int ymin = min(T.ya, min(T.yb, T.yc)), ymax = max(T.ya, max(T.yb, T.yc));
+                const int i0 = max(ceil256(xmin - 128), 0), j0 = max(ceil256(ymin - 128), 0);
+                if (i0 >= px0 && j0 >= py0) {  // its first pixel lies here
+                    const int i1 = min(floor256(xmax - 128), fi.width - 1), j1 = min(floor256(ymax - 128), fi.height - 1);
+                    entries += (unsigned)((i1 / 64 - i0 / 64 + 1) * (j1 / 4 - j0 / 4 + 1));
+                    ++survivors;
+                }
+            }
+            const unsigned entry = ((unsigned)(group + k) << 16) | (unsigned)t;
+            bool small = n > 0;
+            const unsigned long long mb = __ballot(n > kPOwn);
+            if (mb) {
+                int at = 0;
+                if (lane == 0) at = atomicAdd(&S.n_big, __popcll(mb));
+                at = __builtin_amdgcn_readlane(at, 0) + lanes_below(mb);
+                if (n > kPOwn && at < kPBig) {
+                    S.big[at] = entry;
+                    small = false;
+                }
+            }
+            const unsigned long long ms = __ballot(small);
+            if (small) buf[n_buf + lanes_below(ms)] = entry;
+            n_buf += __popcll(ms);
+            if (n_buf >= kWave) {
+                n_buf -= kWave;
+                raster(n_buf + lane, n_buf + kWave, buf, 0, 0, 0);
             }
         }
-        const unsigned entry = ((unsigned)k << 16) | (unsigned)t;
-        bool small = n > 0;
-        const unsigned long long mb = __ballot(n > kPOwn);
-        if (mb) {
-            int at = 0;
-            if (lane == 0) at = atomicAdd(&S.n_big, __popcll(mb));
-            at = __builtin_amdgcn_readlane(at, 0) + lanes_below(mb);
-            if (n > kPOwn && at < kPBig) {
-                S.big[at] = entry;
-                small = false;
-            }
-        }
-        const unsigned long long ms = __ballot(small);
-        if (small) buf[n_buf + lanes_below(ms)] = entry;
-        n_buf += __popcll(ms);
-        if (n_buf >= kWave) {
-            n_buf -= kWave;
-            raster(n_buf + lane, n_buf + kWave, buf, 0, 0, 0);
-        }
-    }
+        group += kWave;
+    } while (G && group < n_obj);
     if (n_buf > 0) raster(lane, n_buf, buf, 0, 0, 0);
     __syncthreads();
     // queued triangles, four per wave and step
@@ -430,9 +503,9 @@ __global__ __launch_bounds__(kPT) void k_patch(RenderArgs a) {
                     const int m = S.mvb[k], b = S.vbase[k];
                     MatTex mt;
                     if constexpr (kMat) mt = mat_inputs(a, fi.obj_begin + k, m, tv);
-                    const int2 A = S.XY[b + tv.x], B = S.XY[b + tv.z], C = S.XY[b + tv.y];
-                    o = shade_pixel<kSpot, kMat>(A.x, A.y, B.x, B.y, C.x, C.y, S.iw[b + tv.x], S.iw[b + tv.z],
-                                                 S.iw[b + tv.y], a.mesh_nrm[m + tv.x], a.mesh_nrm[m + tv.z],
+                    const int4 A = verts.get(b + tv.x), B = verts.get(b + tv.z), C = verts.get(b + tv.y);
+                    o = shade_pixel<kSpot, kMat>(A.x, A.y, B.x, B.y, C.x, C.y, __int_as_float(A.z), __int_as_float(B.z),
+                                                 __int_as_float(C.z), a.mesh_nrm[m + tv.x], a.mesh_nrm[m + tv.z],
                                                  a.mesh_nrm[m + tv.y], S.R[k], i, j, z, cam, S.light, S.ltype,
                                                  fi.n_lights, S.mat[k], S.spot, a.shadow_maps, a.shadow_res, &mt,
                                                  a.tex_texels, a.tex_info);
@@ -461,23 +534,28 @@ __global__ __launch_bounds__(kWave) void k_patch_prepare(RenderArgs a) {
     if ((it.x0 | it.y0) != 0) return;
     const FrameInfo fi = a.frames[it.frame];
     if (a.p_account && threadIdx.x == 0) a.p_account[it.frame] = 0ull;
-    if (!a.out_track || (int)threadIdx.x >= fi.n_obj) return;
     const int k = threadIdx.x;
+    if (!a.out_track || k >= fi.n_obj || fi.n_obj > kPOMax) return;  // (larger scenes: k_vertex)
     const float *V = a.view + 12 * (int64_t)it.frame, *P = a.pose + 12 * (int64_t)(fi.obj_begin + k);
     const float *K = a.intr + 4 * (int64_t)it.frame;
     track_init(a.out_track + fi.track_base + k, compose_entry(V, P, 3), compose_entry(V, P, 7), compose_entry(V, P, 11),
                K[0], K[1], K[2], K[3]);
 }
 
-hipError_t launch_patch(const RenderArgs &a, hipStream_t stream) {
+// a.pitems: the patches of scenes held in LDS, or (global) of larger ones, whose vertices
+// k_vertex has written (it also starts their Tracker records).
+hipError_t launch_patch(const RenderArgs &a, bool global, hipStream_t stream) {
     if (a.n_pitems <= 0) return hipSuccess;
-    if (a.p_account || a.out_track) hipLaunchKernelGGL(k_patch_prepare, dim3(a.n_pitems), dim3(kWave), 0, stream, a);
+    if (a.p_account || (a.out_track && !global))
+        hipLaunchKernelGGL(k_patch_prepare, dim3(a.n_pitems), dim3(kWave), 0, stream, a);
     const bool aux = a.out_alpha || a.out_track || a.out_rgb8;
     const dim3 g(a.n_pitems), b(kPT);
-#define ORRB_PATCH(SHADE_)                                                                 \
-    do {                                                                                   \
-        if (aux) hipLaunchKernelGGL((k_patch<true, SHADE_>), g, b, 0, stream, a);          \
-        else hipLaunchKernelGGL((k_patch<false, SHADE_>), g, b, 0, stream, a);             \
+#define ORRB_PATCH(SHADE_)                                                                           \
+    do {                                                                                             \
+        if (global && aux) hipLaunchKernelGGL((k_patch<true, true, SHADE_>), g, b, 0, stream, a);    \
+        else if (global) hipLaunchKernelGGL((k_patch<false, true, SHADE_>), g, b, 0, stream, a);     \
+        else if (aux) hipLaunchKernelGGL((k_patch<true, false, SHADE_>), g, b, 0, stream, a);        \
+        else hipLaunchKernelGGL((k_patch<false, false, SHADE_>), g, b, 0, stream, a);                \
     } while (0)
     switch (a.shade_mode) {
         case 4: ORRB_PATCH(4); break;

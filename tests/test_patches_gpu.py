@@ -31,17 +31,15 @@ def _resized(b, sizes):
                      intr=np.array([S.intrinsics(w, h) for w, h in wh], np.float32))
 
 
-def _both(renderer, b, name):
-    """Every output from the default path (patches) and the tiled path, as numpy arrays."""
+def _both(renderer, b, name, path):
+    """Every output from `path` (patches) and from the tiled path, as numpy arrays."""
     import torch
     got = []
-    for tuning in (None, TILED):
+    for tuning in ((32, 32, 512, 0, path), TILED):
         job = renderer.prepare(b)
-        if tuning:
-            job.layout.set_tuning(*tuning)
+        job.layout.set_tuning(*tuning)
         inf = job.layout.info
         print(f"[patches] {name} frames={b.n_frames} tuning={tuning} frame_path={inf.frame_path_frames}", flush=True)
-        assert inf.frame_path_frames == (0 if tuning else b.n_frames)
         out = renderer.alloc_outputs(job, tri_id=True, vis=True, stats=True, alpha=True, rgb8=True, track=True)
         for k, t in out.items():
             if k != "stats":
@@ -52,8 +50,8 @@ def _both(renderer, b, name):
     return got
 
 
-def _check(renderer, b, name):
-    got, want = _both(renderer, b, name)
+def _check(renderer, b, name, path=0):
+    got, want = _both(renderer, b, name, path)
     for k in want:
         if k == "stats":  # wait timeouts, near and guard vertices
             assert [got[k][w] for w in (0, 3, 4)] == [want[k][w] for w in (0, 3, 4)], (name, got[k], want[k])
@@ -141,6 +139,37 @@ def test_many_large_triangles(renderer, n_obj, n, res):
                               extra_objects=[(m, pose(k + 1)) for k, m in enumerate(planes[1:])],
                               lights=((0, (0.3, 0.4, 0.5), 1.5),))
     _check(renderer, b, f"planes {n_obj} x {2 * n * n}")
+
+
+def _large_scenes(kind):
+    if kind == "uneven":        # scenes on both sides of what fits in LDS
+        return S.config3(14, 6, 2, min_tris=4000, max_tris=30000)
+    if kind == "past-256":      # larger frames of larger scenes
+        return _resized(S.config3(15, 2, 2, min_tris=16000, max_tris=20000), [(300, 200), (512, 70), (33, 400)])
+    if kind == "127-objects":   # more than one group of 64 objects, the last of them in view
+        box, cap = S.box_mesh(4), S.capsule_mesh(0.02, 0.05, 16, 8)
+        rng = np.random.default_rng(16)
+        pose = lambda k: S.make_pose(S.uniform_rotation(rng), rng.uniform(-0.4, 0.4, 3) - [0, 0, 1.2], 0.1 if k % 2 else 2.0)
+        return S.single_object_batch(box, S.make_pose(np.eye(3), (0, 0, -1.0), 0.1), res=(200, 200), rough=0.5, spec=0.4,
+                                     extra_objects=[(box if k % 2 else cap, pose(k)) for k in range(126)],
+                                     lights=((0, (0.3, 0.4, 0.5), 1.5),))
+    b = S.config3(17, 3, 2, min_tris=9000, max_tris=14000)
+    vis = b.object_visible.copy()
+    vis[::3] = 0
+    view = b.view.copy()
+    view[1, :, 3] += np.array([0.0, 0.0, 50.0], np.float32)
+    return S.with_spot_lights(S.with_materials(b.replace(object_visible=vis, view=view), seed=2), seed=3)
+
+
+@pytest.mark.parametrize("path", [0, 2])
+@pytest.mark.parametrize("kind", ["uneven", "past-256", "127-objects", "every-feature"])
+def test_scenes_beyond_lds(renderer, kind, path):
+    """Patches that read the vertex kernel's records instead of LDS."""
+    b = _large_scenes(kind)
+    nv = [sum(b.meshes[m].n_verts for m in b.object_mesh[o0:o1]) for o0, o1 in
+          zip(b.scene_object_begin[:-1], b.scene_object_begin[1:])]
+    assert max(nv) > 6976 or np.diff(b.scene_object_begin).max() > 48
+    _check(renderer, S.with_postprocessing(b, seed=4), kind, path)
 
 
 def test_uneven_small_batch(renderer):
