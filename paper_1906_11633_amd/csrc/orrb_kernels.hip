@@ -377,7 +377,7 @@ ORRB_INLINE void raster_shade_tile(const RenderArgs &a, int item, LD &L) {
             triv = tri;
         }
         store_pixel(a, po, HW, pix, o, z, segv, triv, key);
-        if (fused) store_rgb8(a, pq, po, HW, pix, i, j, o);
+        if (fused) store_rgb8(a, pq, po, HW, pix, i, j, post_grade(pq, o.r0, o.r1, o.r2));
     }
 
     // ---- tracker: every lane of a wave takes part (the trip count is uniform) ----

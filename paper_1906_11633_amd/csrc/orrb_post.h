@@ -169,9 +169,9 @@ ORRB_INLINE unsigned grain_texel(const RenderArgs &a, const PostFrame &q, int i,
     return (unsigned)(ty * a.grain_w + tx) * 4u;
 }
 
-// The 8-bit codes of pixel (i, j), linear rgb in o, stored to the three byte planes.
+// The 8-bit codes of pixel (i, j), graded value o (post_grade), stored to the three byte planes.
 ORRB_INLINE void store_rgb8(const RenderArgs &a, const PostFrame &q, int64_t po, int64_t HW, int64_t pix, int i, int j,
-                            const PixelOut &o) {
+                            float3 o) {
     float n0 = 0.f, n1 = 0.f, n2 = 0.f;
     if (q.gi != 0.f) {
         const unsigned t = grain_texel(a, q, i, j);
@@ -179,7 +179,7 @@ ORRB_INLINE void store_rgb8(const RenderArgs &a, const PostFrame &q, int64_t po,
         n1 = grain_at(q.g1, t);
         n2 = grain_at(q.g2, t);
     }
-    const uchar3 u = post_pixel(q, o.r0, o.r1, o.r2, n0, n1, n2);
+    const uchar3 u = post_final(q, o, n0, n1, n2);
     uint8_t *d = a.out_rgb8 + 3 * po + pix;
     d[0] = u.x;
     d[HW] = u.y;
