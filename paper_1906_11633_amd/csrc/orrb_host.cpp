@@ -336,37 +336,53 @@ static void schedule_frames(orrb_layout *L) {
     L->f_dynamic = 1;
 }
 
-// Cut a frame into patches, a grid of columns (of whole 4-pixel units) and rows whose cells
-// hold at most `cap` pixels.  More than the least number of patches are asked for
-// where they all run at once: the frame is cut into `parts` strips of its width (of 256
-// pixels or so of a wider frame), which share out what the middle of the frame shows.
-// Otherwise (batches of several rounds, where the geometry each patch repeats counts) into
-// the least number of columns, in two or more rows where a column would be narrower than 28
-// pixels: hand scenes, 120 frames of 200 x 200, 79 us in 7 columns and 85 us in 7 rows; 48
-// frames of 128 x 128, 33 us in 6 rows, 38 us in 2 x 3 cells.
-static void patch_grid(int W, int H, int cap, int parts, int *cols, int *rows) {
+// Grid of columns (of whole 4-pixel units) and rows that cuts a W x H frame into patches of at
+// most `cap` pixels; `share`: the CUs there are for it; `narrow`: columns below 28 pixels may
+// be used.  They write part of each 128-byte line, which costs bandwidth once a batch's outputs
+// no longer fit the 256 MB cache, some 8 M pixels (148 hand frames of 256 x 256: 124 us in
+// 5 x 2 cells, 135 in 10 columns; 104 frames: 108 and 92).
+//   - Many CUs: strips of the frame's width (of 256 pixels or so of a wider frame), a few more
+//     than the CUs, as the outer ones are light; frames beyond 256 x 256, whose outer patches
+//     are often empty, twice as many.  48 hand frames of 128 x 128: 33 us in 6 rows, 37 in 6
+//     columns; 12 of 200 x 200: 23 in 24 rows, 26 in 3 x 12.
+//     Small frames down to 3 rows (68 of 88 x 88: 37 us, 38 in 7 columns), others from 5 on.
+//   - Few: as few patches as the pixels allow, since each repeats geometry, and in columns,
+//     which repeat less than rows (hand scenes, 120 frames of 200 x 200, 77 us in 7 columns, 85
+//     in 7 rows), none narrower than 28 pixels.
+//   - Between (1.7 CUs and more a frame): up to 1.9 columns a CU and frame, of 18 pixels or
+//     more, so that two rounds even out (72 frames of 128 x 128: 50 us in 3 columns, 41 in 6;
+//     144 of 64 x 64: 41 us whole, 55 in 2, 39 in 3), unless two rows just fill the chip
+//     or three columns are needed anyhow and there are few CUs (120 of 128 x 128: 51 us in
+//     3 columns, 55 in 4).
+static void patch_grid(int W, int H, int cap, double share, bool narrow, int *cols, int *rows) {
     constexpr int U = 4;
-    const int nx = (W + U - 1) / U;
+    const int nx = (W + U - 1) / U, side = frame_max_side();
+    const bool large = W > side || H > side, some = !large && narrow && share >= 1.7;
     auto fits = [&](int x, int y) { return (int64_t)U * ((nx + x - 1) / x) * ((H + y - 1) / y) <= cap; };
     int x = 1, y = 1;
-    for (y = 1; y <= H; ++y) {
+    for (y = 1; y <= H; ++y) {  // the least number of columns, in more rows where they get too narrow
         for (x = 1; x < nx && !fits(x, y); ++x) {
         }
-        if (fits(x, y) && (x == 1 || W >= 28 * x)) break;
+        if (fits(x, y) && (x == 1 || W >= (some ? 18 : 28) * x)) break;
     }
-    if (y > H) y = H;  // (a column of one unit is always narrow enough: U * H rows <= cap at y = H)
-    if (parts > x * y) {
-        x = std::max(1, std::min(nx, (W + 128) / 256));
-        for (y = std::max(1, std::min(H, parts / x)); y < H && !fits(x, y); ++y) {
-        }
+    if (y > H) y = H;  // (one row of pixels always fits)
+    const int wide = std::max(1, std::min(nx, (W + 128) / 256));
+    const bool pair = !large && share >= 2.0 && share <= 2.2;  // two rows fill one round
+    const int strips = std::min(H, (int)((large ? 2.0 : 1.125) * share / wide));
+    if ((large || pair || strips >= (x * y <= 2 && share >= 3.3 ? 3 : 5)) && wide * strips >= x * y && fits(wide, strips)) {
+        x = wide;
+        y = strips;
+    } else if (some && y == 1 && (x < 3 || share >= 2.45)) {
+        x = std::max(x, std::min({nx, W / 18, (int)(1.9 * share)}));
     }
     *cols = x;
     *rows = y;
 }
 
-static void cut_frame(const FrameInfo &fi, int32_t f, int cap, int parts, std::vector<PatchItem> &out) {
+static void cut_frame(const FrameInfo &fi, int32_t f, int cap, double share, bool narrow,
+                      std::vector<PatchItem> &out) {
     int px, py;
-    patch_grid(fi.width, fi.height, cap, parts, &px, &py);
+    patch_grid(fi.width, fi.height, cap, share, narrow, &px, &py);
     const int nx = (fi.width + 3) / 4;
     for (int y = 0; y < py; ++y)
         for (int x = 0; x < px; ++x) {
@@ -423,20 +439,18 @@ static void choose_patches(const orrb_layout *L, std::vector<int32_t> &frames, b
     patched.insert(patched.end(), rest.begin() + keep, rest.end());
 }
 
-// The patches: enough of them to fill the CUs a little more than once (twice for frames
-// beyond 256 x 256, whose outer patches are often empty), the costlier frames cut into more.
+// The patches of frames `patched`: the CUs are shared out by estimated work.
 static void schedule_patches(const orrb_layout *L, const std::vector<int32_t> &patched, bool global,
                              std::vector<PatchItem> &items) {
     const int64_t n_cu = L->ctx ? L->ctx->n_cu : 256;
-    const int side = frame_max_side(), cap = patch_max_pixels(global);
+    const int cap = patch_max_pixels(global);
     items.clear();
     double total = 0.0;
     for (int32_t f : patched) total += frame_cost(L, f, false);
-    for (int32_t f : patched) {
-        const FrameInfo &fi = L->frames[f];
-        const double over = fi.width > side || fi.height > side ? 2.0 : 1.125;
-        cut_frame(fi, f, cap, (int)(over * (double)n_cu * frame_cost(L, f, false) / total), items);
-    }
+    int64_t pixels = 0;
+    for (const FrameInfo &fi : L->frames) pixels += (int64_t)fi.width * fi.height;
+    for (int32_t f : patched)
+        cut_frame(L->frames[f], f, cap, (double)n_cu * frame_cost(L, f, false) / total, pixels <= 8 << 20, items);
     // The middle of a frame usually shows the most: patches nearest to their frame's centre
     // first, so that the last ones to run are light, and the same patch of consecutive
     // frames on consecutive XCDs (in frame order, eight patches a frame put all the middle

@@ -206,3 +206,9 @@ def test_graph_replays(renderer):
         _ = torch.randn(1000, device="cuda").sum().item()
     assert int(out["stats"][0]) == 0
     g.close()
+
+
+@pytest.mark.parametrize("frames,res", [(56, 90), (58, 90), (78, 61), (126, 256), (114, 61), (117, 61), (104, 130), (106, 130), (129, 130), (150, 61), (152, 61)])
+def test_grids_of_middle_batches(renderer, frames, res):
+    """Both sides of each line between strips, pairs of rows, several columns and the fewest."""
+    _check(renderer, S.config2(14, frames, res, 1), f"{frames} frames of {res}")
