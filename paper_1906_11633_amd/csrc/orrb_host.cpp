@@ -337,10 +337,13 @@ static void schedule_frames(orrb_layout *L) {
 }
 
 // Grid of columns (of whole 4-pixel units) and rows that cuts a W x H frame into patches of at
-// most `cap` pixels; `share`: the CUs there are for it; `narrow`: columns below 28 pixels may
-// be used.  They write part of each 128-byte line, which costs bandwidth once a batch's outputs
-// no longer fit the 256 MB cache, some 8 M pixels (148 hand frames of 256 x 256: 124 us in
-// 5 x 2 cells, 135 in 10 columns; 104 frames: 108 and 92).
+// most `cap` pixels.  `share`: the CUs there are for it.  `heavy`: its geometry is worth
+// sharing out finely and the batch's rounds can be foreseen: 2,048 triangles and more held in
+// LDS, frames of one cost (231 mixed frames: 216 us without and 230 with the finer grids, 322:
+// 267 and 276, 131 frames of one capsule: 20.3 and 21.5).  `narrow`: columns below 28 pixels may be
+// used.  They write part of each 128-byte line, which costs bandwidth once a batch's
+// outputs no longer fit the 256 MB cache, some 8 M pixels (148 hand frames of 256 x 256: 124 us
+// in 5 x 2 cells, 135 in 10 columns; 104 frames: 108 and 92).
 //   - Many CUs: strips of the frame's width (of 256 pixels or so of a wider frame), a few more
 //     than the CUs, as the outer ones are light; frames beyond 256 x 256, whose outer patches
 //     are often empty, twice as many.  48 hand frames of 128 x 128: 33 us in 6 rows, 37 in 6
@@ -354,10 +357,11 @@ static void schedule_frames(orrb_layout *L) {
 //     144 of 64 x 64: 41 us whole, 55 in 2, 39 in 3), unless two rows just fill the chip
 //     or three columns are needed anyhow and there are few CUs (120 of 128 x 128: 51 us in
 //     3 columns, 55 in 4).
-static void patch_grid(int W, int H, int cap, double share, bool narrow, int *cols, int *rows) {
+static void patch_grid(int W, int H, int cap, double share, bool heavy, bool narrow, int *cols,
+                       int *rows) {
     constexpr int U = 4;
     const int nx = (W + U - 1) / U, side = frame_max_side();
-    const bool large = W > side || H > side, some = !large && narrow && share >= 1.7;
+    const bool large = W > side || H > side, some = !large && heavy && narrow && share >= 1.7;
     auto fits = [&](int x, int y) { return (int64_t)U * ((nx + x - 1) / x) * ((H + y - 1) / y) <= cap; };
     int x = 1, y = 1;
     for (y = 1; y <= H; ++y) {  // the least number of columns, in more rows where they get too narrow
@@ -367,9 +371,10 @@ static void patch_grid(int W, int H, int cap, double share, bool narrow, int *co
     }
     if (y > H) y = H;  // (one row of pixels always fits)
     const int wide = std::max(1, std::min(nx, (W + 128) / 256));
-    const bool pair = !large && share >= 2.0 && share <= 2.2;  // two rows fill one round
+    const bool pair = share >= 2.0 && share <= 2.2;  // two rows fill one round
     const int strips = std::min(H, (int)((large ? 2.0 : 1.125) * share / wide));
-    if ((large || pair || strips >= (x * y <= 2 && share >= 3.3 ? 3 : 5)) && wide * strips >= x * y && fits(wide, strips)) {
+    const int least = large || pair || !heavy ? 1 : x * y <= 2 && share >= 3.1 ? 3 : 5;
+    if (strips >= least && wide * strips > x * y && fits(wide, strips)) {
         x = wide;
         y = strips;
     } else if (some && y == 1 && (x < 3 || share >= 2.45)) {
@@ -379,10 +384,10 @@ static void patch_grid(int W, int H, int cap, double share, bool narrow, int *co
     *rows = y;
 }
 
-static void cut_frame(const FrameInfo &fi, int32_t f, int cap, double share, bool narrow,
+static void cut_frame(const FrameInfo &fi, int32_t f, int cap, double share, bool heavy, bool narrow,
                       std::vector<PatchItem> &out) {
     int px, py;
-    patch_grid(fi.width, fi.height, cap, share, narrow, &px, &py);
+    patch_grid(fi.width, fi.height, cap, share, heavy, narrow, &px, &py);
     const int nx = (fi.width + 3) / 4;
     for (int y = 0; y < py; ++y)
         for (int x = 0; x < px; ++x) {
@@ -446,11 +451,16 @@ static void schedule_patches(const orrb_layout *L, const std::vector<int32_t> &p
     const int cap = patch_max_pixels(global);
     items.clear();
     double total = 0.0;
-    for (int32_t f : patched) total += frame_cost(L, f, false);
+    bool uniform = !patched.empty();
+    for (int32_t f : patched) {
+        total += frame_cost(L, f, false);
+        uniform = uniform && frame_cost(L, f, false) == frame_cost(L, patched[0], false);
+    }
     int64_t pixels = 0;
     for (const FrameInfo &fi : L->frames) pixels += (int64_t)fi.width * fi.height;
     for (int32_t f : patched)
-        cut_frame(L->frames[f], f, cap, (double)n_cu * frame_cost(L, f, false) / total, pixels <= 8 << 20, items);
+        cut_frame(L->frames[f], f, cap, (double)n_cu * frame_cost(L, f, false) / total,
+                  !global && uniform && L->scene_tris[L->frames[f].scene] >= 2048, pixels <= 8 << 20, items);
     // The middle of a frame usually shows the most: patches nearest to their frame's centre
     // first, so that the last ones to run are light, and the same patch of consecutive
     // frames on consecutive XCDs (in frame order, eight patches a frame put all the middle
