@@ -1416,9 +1416,7 @@ ORRB_INLINE bool frame_render(const RenderArgs &a, FrameLds &S, int item, int se
             if (t < n_tiles) {
                 S.off[t] = run;
                 S.cnt[t] = run;  // becomes the scatter cursor
-                // without bins every tile is rasterized, in plain order; otherwise tiles
-                // with entries first
-                S.order[overflow ? t : (c[q] > 0 ? run_ne : total_ne + t - run_ne)] = (unsigned char)t;
+                S.order[c[q] > 0 ? run_ne : total_ne + t - run_ne] = (unsigned char)t;  // tiles with entries first
             }
             run += c[q];
             run_ne += c[q] > 0;
@@ -1427,203 +1425,246 @@ ORRB_INLINE bool frame_render(const RenderArgs &a, FrameLds &S, int item, int se
             S.off[n_tiles] = incl;
             S.misc[2] = incl;
             S.misc[1] = overflow;
-            S.misc[4] = overflow ? n_tiles : total_ne;
+            S.misc[4] = total_ne;
             stat_add(a, ORRB_STAT_BIN_OVERFLOW, overflow ? 1u : 0u);
         }
         // queue the tiles no triangle touches for the store waves
-        const int n_busy = overflow ? n_tiles : total_ne;
-        frame_publish(a, S, seq, f, fi.pixel_offset, W, H, ntx, n_busy, n_tiles, lane);
+        frame_publish(a, S, seq, f, fi.pixel_offset, W, H, ntx, total_ne, n_tiles, lane);
     }
     if (frame_barrier<G>(a, S, gen)) return true;
     const bool overflow = S.misc[1] != 0;
 
-    // ---- phase 3: scatter triangle IDs into the tile bins ----
-    const int n_surv = S.misc[3];
-    if (!overflow && n_surv <= F.surv_max) {
-        for (int k = tid; k < n_surv; k += kFCT) {
-            const unsigned e = F.surv[k];
-            const int tx0 = e & 3, tx1 = (e >> 2) & 3, ty0 = (e >> 4) & 63, ty1 = (e >> 10) & 63;
-            for (int ty = ty0; ty <= ty1; ++ty)
-                for (int tx = tx0; tx <= tx1; ++tx) F.bin[atomicAdd(&S.cnt[ty * ntx + tx], 1)] = (unsigned short)(e >> 16);
-        }
-    } else if (!overflow) {  // too many survivors to remember: set them up again
-        if (tid == 0) stat_add(a, ORRB_STAT_SURVIVOR_RESETUP, 1u);
-        for (int t = tid; t < n_tris; t += kFCT) {
-            const int k = slot_hint(F.o_tbase, n_obj, S.tri_hint, t);
-            TriSetup T;
-            if (!frame_setup(F, k, frame_tri(a, F, k, t), 0, 0, W - 1, H - 1, T)) continue;
-            for (int ty = (unsigned)T.j0 / kFTileH; ty <= (int)((unsigned)T.j1 / kFTileH); ++ty)
-                for (int tx = (unsigned)T.i0 / kFTileW; tx <= (int)((unsigned)T.i1 / kFTileW); ++tx)
-                    F.bin[atomicAdd(&S.cnt[ty * ntx + tx], 1)] = (unsigned short)t;
-        }
-    }
-    if (frame_barrier<G>(a, S, gen)) return true;
-
-    // ---- phase 4: compute waves take the tiles with bin entries, rasterize, shade and
-    // write them, issuing all loads of a tile before its stores; the store waves write
-    // the rest meanwhile.
+    // Phases 3 and 4 run once over all tiles with entries where these fit the bins.  Otherwise
+    // (hand scenes beyond 230 x 230) the tiles are worked through in groups, each the longest
+    // run of tiles whose entries fit, with the triangles set up again for every group after the
+    // first (the survivor list's LDS holds the tile keys by then): 768 hand frames of 256 x 256,
+    // 490 us (every busy tile scanning all triangles: 6,865).  A tile with more entries than
+    // the bins hold scans all triangles, and so does every tile where groups would on average
+    // hold fewer tiles than there are compute waves.
+    const int n_busy = S.misc[4], n_surv = S.misc[3];
     const CamF cam = frame_camera(a, f);
     const int64_t HW = (int64_t)W * H, po = fi.pixel_offset;
-    const int n_busy = S.misc[4];
     const bool vec_frame = frame_vec(a, W, po);
-    unsigned long long *vis = S.u.vis[wave];
-    bool stopped = false;
-    while (!stopped) {
-        int slot = 0;
-        if (lane == 0) slot = atomicAdd(&S.misc[0], 1);
-        slot = __builtin_amdgcn_readlane(slot, 0);
-        if (slot >= n_busy) {
-            if (slot == n_busy) frame_next(a, S, item, seq, lane);
-            if constexpr (AUX) frame_bg_help<AUX>(a, S, seq, lj, li0, lane);
-            break;
-        }
-        const int t = S.order[slot];
-        const int tyi = t / ntx, txi = t - tyi * ntx;
-        const int x0 = txi * kFTileW, y0 = tyi * kFTileH;
-        const int x1 = min(x0 + kFTileW, W) - 1, y1 = min(y0 + kFTileH, H) - 1;
-        const int j = y0 + lj, i0 = x0 + li0;
-        const int n_in = j <= y1 ? max(0, min(4, x1 - i0 + 1)) : 0;
-        const int64_t gpix = (int64_t)j * W + i0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) vis[lane + 64 * q] = kEmptyKey;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        // Keys in the LDS tile carry the triangle's object slot in bits 16..23 above its
-        // 16-bit ID: slots do not decrease with the ID, so the (depth, ID) order is
-        // unchanged, shading needs no object lookup, and the bits are cleared before the
-        // key leaves the tile.  Without bins (overflow) the wave scans every triangle.
-        const int e0 = overflow ? 0 : S.off[t], e1 = overflow ? n_tris : S.off[t + 1];
-        for (int e = e0 + lane; e < e1; e += kWave) {
-            const int tri = overflow ? e : (int)F.bin[e];
-            const int k = slot_hint(F.o_tbase, n_obj, S.tri_hint, tri);
-            TriSetup T;
-            int flags;
-            float area;
-            if (overflow) {  // unbinned: the full culling set-up
-                if (!frame_setup(F, k, frame_tri(a, F, k, tri), x0, y0, x1, y1, T)) continue;
-                flags = tri_flags(T.xa, T.ya, T.xb, T.yb, T.xc, T.yc);
-                area = (float)T.area;
-                T.iwa = __int_as_float(F.vall(T.va).z);
-                T.iwb = __int_as_float(F.vall(T.vb).z);
-                T.iwc = __int_as_float(F.vall(T.vc).z);
-            } else if (!tile_setup(F, k, frame_tri(a, F, k, tri), x0, y0, x1, y1, T, flags, area)) {
-                continue;
+    const bool scan_all = overflow && S.misc[2] > n_busy * (F.bin_max / kFCW);
+    int s0 = 0;
+    do {
+        int s1 = n_busy;  // the group: slots s0 .. s1 - 1 of the tile order, tiles ta .. tb
+        int ta = 0, tb = n_tiles - 1, ebase = 0;
+        bool scan = scan_all;
+        if (overflow && !scan_all) {
+            ta = S.order[s0];
+            ebase = S.off[ta];
+            int lo = s0 + 1, hi = n_busy;  // the largest end whose entries fit (one tile at least)
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (S.off[S.order[mid - 1] + 1] - ebase <= F.bin_max)
+                    lo = mid;
+                else
+                    hi = mid - 1;
             }
-            const float iwa = T.iwa, iwb = T.iwb, iwc = T.iwc;
-            if (!(flags & 8)) {  // small triangle: step the integer edge functions
-                const int b0 = (flags & 1) ? 0 : 1, b1 = (flags & 2) ? 0 : 1, b2 = (flags & 4) ? 0 : 1;
-                EdgeStep es = edge_start(T.xa, T.ya, T.xb, T.yb, T.xc, T.yc, (T.i0 << 8) + 128, (T.j0 << 8) + 128);
-                for (int jj = T.j0; jj <= T.j1; ++jj) {
-                    int e0 = es.e0, e1 = es.e1, e2 = es.e2;
-                    for (int ii = T.i0; ii <= T.i1; ++ii) {
-                        if (((e0 - b0) | (e1 - b1) | (e2 - b2)) >= 0) {
-                            Edges ed;
-                            ed.e0 = (float)e0;
-                            ed.e1 = (float)e1;
-                            ed.e2 = (float)e2;
+            s1 = lo;
+            tb = S.order[s1 - 1];
+            scan = S.off[tb + 1] - ebase > F.bin_max;
+            if (tid == 0) S.misc[0] = s0;
+        }
+
+        // ---- phase 3: scatter triangle IDs into the tile bins ----
+        auto scatter = [&](int id, int tx0, int tx1, int ty0, int ty1) {
+            for (int ty = ty0; ty <= ty1; ++ty)
+                for (int tx = tx0; tx <= tx1; ++tx) {
+                    const int t = ty * ntx + tx;
+                    if (t >= ta && t <= tb) F.bin[atomicAdd(&S.cnt[t], 1) - ebase] = (unsigned short)id;
+                }
+        };
+        if (!overflow && n_surv <= F.surv_max) {  // the usual frame: one group
+            for (int k = tid; k < n_surv; k += kFCT) {
+                const unsigned e = F.surv[k];
+                const int tx0 = e & 3, tx1 = (e >> 2) & 3, ty0 = (e >> 4) & 63, ty1 = (e >> 10) & 63;
+                for (int ty = ty0; ty <= ty1; ++ty)
+                    for (int tx = tx0; tx <= tx1; ++tx)
+                        F.bin[atomicAdd(&S.cnt[ty * ntx + tx], 1)] = (unsigned short)(e >> 16);
+            }
+        } else if (!scan && s0 == 0 && n_surv <= F.surv_max) {
+            for (int k = tid; k < n_surv; k += kFCT) {
+                const unsigned e = F.surv[k];
+                scatter(e >> 16, e & 3, (e >> 2) & 3, (e >> 4) & 63, (e >> 10) & 63);
+            }
+        } else if (!scan) {  // too many survivors to remember, or overwritten: set them up again
+            if (tid == 0) stat_add(a, ORRB_STAT_SURVIVOR_RESETUP, overflow ? 0u : 1u);
+            for (int t = tid; t < n_tris; t += kFCT) {
+                const int k = slot_hint(F.o_tbase, n_obj, S.tri_hint, t);
+                TriSetup T;
+                if (!frame_setup(F, k, frame_tri(a, F, k, t), 0, 0, W - 1, H - 1, T)) continue;
+                scatter(t, (unsigned)T.i0 / kFTileW, (unsigned)T.i1 / kFTileW, (unsigned)T.j0 / kFTileH,
+                        (unsigned)T.j1 / kFTileH);
+            }
+        }
+        if (frame_barrier<G>(a, S, gen)) return true;
+
+        // ---- phase 4: compute waves take the tiles with bin entries, rasterize, shade and
+        // write them, issuing all loads of a tile before its stores; the store waves write
+        // the rest meanwhile.
+        unsigned long long *vis = S.u.vis[wave];
+        bool stopped = false;
+        while (!stopped) {
+            int slot = 0;
+            if (lane == 0) slot = atomicAdd(&S.misc[0], 1);
+            slot = __builtin_amdgcn_readlane(slot, 0);
+            if (slot >= s1) {
+                if (slot == n_busy) frame_next(a, S, item, seq, lane);
+                if (AUX && s1 == n_busy) frame_bg_help<AUX>(a, S, seq, lj, li0, lane);
+                break;
+            }
+            const int t = S.order[slot];
+            const int tyi = t / ntx, txi = t - tyi * ntx;
+            const int x0 = txi * kFTileW, y0 = tyi * kFTileH;
+            const int x1 = min(x0 + kFTileW, W) - 1, y1 = min(y0 + kFTileH, H) - 1;
+            const int j = y0 + lj, i0 = x0 + li0;
+            const int n_in = j <= y1 ? max(0, min(4, x1 - i0 + 1)) : 0;
+            const int64_t gpix = (int64_t)j * W + i0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) vis[lane + 64 * q] = kEmptyKey;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            // Keys in the LDS tile carry the triangle's object slot in bits 16..23 above its
+            // 16-bit ID: slots do not decrease with the ID, so the (depth, ID) order is
+            // unchanged, shading needs no object lookup, and the bits are cleared before the
+            // key leaves the tile.
+            const int e0 = scan ? 0 : S.off[t] - ebase, e1 = scan ? n_tris : S.off[t + 1] - ebase;
+            for (int e = e0 + lane; e < e1; e += kWave) {
+                const int tri = scan ? e : (int)F.bin[e];
+                const int k = slot_hint(F.o_tbase, n_obj, S.tri_hint, tri);
+                TriSetup T;
+                int flags;
+                float area;
+                if (scan) {  // unbinned: the full culling set-up
+                    if (!frame_setup(F, k, frame_tri(a, F, k, tri), x0, y0, x1, y1, T)) continue;
+                    flags = tri_flags(T.xa, T.ya, T.xb, T.yb, T.xc, T.yc);
+                    area = (float)T.area;
+                    T.iwa = __int_as_float(F.vall(T.va).z);
+                    T.iwb = __int_as_float(F.vall(T.vb).z);
+                    T.iwc = __int_as_float(F.vall(T.vc).z);
+                } else if (!tile_setup(F, k, frame_tri(a, F, k, tri), x0, y0, x1, y1, T, flags, area)) {
+                    continue;
+                }
+                const float iwa = T.iwa, iwb = T.iwb, iwc = T.iwc;
+                if (!(flags & 8)) {  // small triangle: step the integer edge functions
+                    const int b0 = (flags & 1) ? 0 : 1, b1 = (flags & 2) ? 0 : 1, b2 = (flags & 4) ? 0 : 1;
+                    EdgeStep es = edge_start(T.xa, T.ya, T.xb, T.yb, T.xc, T.yc, (T.i0 << 8) + 128, (T.j0 << 8) + 128);
+                    for (int jj = T.j0; jj <= T.j1; ++jj) {
+                        int e0 = es.e0, e1 = es.e1, e2 = es.e2;
+                        for (int ii = T.i0; ii <= T.i1; ++ii) {
+                            if (((e0 - b0) | (e1 - b1) | (e2 - b2)) >= 0) {
+                                Edges ed;
+                                ed.e0 = (float)e0;
+                                ed.e1 = (float)e1;
+                                ed.e2 = (float)e2;
+                                atomicMin(&vis[(jj - y0) * kFTileW + (ii - x0)], vis_key(fragment_depth(ed, iwa, iwb, iwc, area), tri | (k << 16)));
+                            }
+                            e0 += es.dx0;
+                            e1 += es.dx1;
+                            e2 += es.dx2;
+                        }
+                        es.e0 += es.dy0;
+                        es.e1 += es.dy1;
+                        es.e2 += es.dy2;
+                    }
+                } else {
+                    for (int jj = T.j0; jj <= T.j1; ++jj) {
+                        for (int ii = T.i0; ii <= T.i1; ++ii) {
+                            const Edges ed = edge_eval(T.xa, T.ya, T.xb, T.yb, T.xc, T.yc, (ii << 8) + 128, (jj << 8) + 128, flags);
+                            if (!ed.covered) continue;
                             atomicMin(&vis[(jj - y0) * kFTileW + (ii - x0)], vis_key(fragment_depth(ed, iwa, iwb, iwc, area), tri | (k << 16)));
                         }
-                        e0 += es.dx0;
-                        e1 += es.dx1;
-                        e2 += es.dx2;
-                    }
-                    es.e0 += es.dy0;
-                    es.e1 += es.dy1;
-                    es.e2 += es.dy2;
-                }
-            } else {
-                for (int jj = T.j0; jj <= T.j1; ++jj) {
-                    for (int ii = T.i0; ii <= T.i1; ++ii) {
-                        const Edges ed = edge_eval(T.xa, T.ya, T.xb, T.yb, T.xc, T.yc, (ii << 8) + 128, (jj << 8) + 128, flags);
-                        if (!ed.covered) continue;
-                        atomicMin(&vis[(jj - y0) * kFTileW + (ii - x0)], vis_key(fragment_depth(ed, iwa, iwb, iwc, area), tri | (k << 16)));
                     }
                 }
             }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
 
-        // covered pixels of the lane's group, then the wave's list of covered pixels
-        int covq = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if (q < n_in && vis[lj * kFTileW + li0 + q] != kEmptyKey) covq |= 1 << q;
-        unsigned char *list = S.cov[wave];
-        int n_cov = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const bool c = (covq >> q) & 1;
-            const unsigned long long m = __ballot(c);
-            if (c) list[n_cov + lanes_below(m)] = (unsigned char)(lj * kFTileW + li0 + q);
-            n_cov += __popcll(m);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        if (AUX && a.out_track) {  // tracker: the object slot of each covered pixel's key
-            int sl[4];
+            // covered pixels of the lane's group, then the wave's list of covered pixels
+            int covq = 0;
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                sl[q] = (covq >> q) & 1 ? (int)((unsigned)vis[lj * kFTileW + li0 + q] >> 16) & 0xff : -1;
-            track_tile(a.out_track + fi.track_base, sl, x0 + li0, y0 + lj);  // frames of at most 256 x 256
-        }
-
-        // shade the covered pixels, lane-compacted (lane takes list[lane + 64 r]), in
-        // passes of (up to) two per lane and put them, over the tile's background, into a
-        // staging slot that a store wave writes out
-        int stg = -1;
-        for (int r0 = 0; r0 * kWave < n_cov; r0 += 2) {
-            PixelOut o[2];
-            unsigned long long kk[2];
-            int sg[2], pl[2];
+                if (q < n_in && vis[lj * kFTileW + li0 + q] != kEmptyKey) covq |= 1 << q;
+            unsigned char *list = S.cov[wave];
+            int n_cov = 0;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                kk[h] = kEmptyKey;
-                sg[h] = -1;
-                pl[h] = 0;
-                const int c = (r0 + h) * kWave + lane;
-                if (c >= n_cov) continue;
-                const int p = list[c];
-                const int pi = x0 + (int)((unsigned)p % kFTileW), pj = y0 + (int)((unsigned)p / kFTileW);
-                const unsigned long long key = vis[p];
-                const int tri = (int)(unsigned)(key & 0xffffu), k = (int)(unsigned)((key >> 16) & 0xffu);
-                const float z = __uint_as_float((unsigned)(key >> 32));
-                const int4 tv = frame_tri(a, F, k, tri);
-                const int vb = F.o_vbase[k], mvb = F.o_mvb[k];
-                const int va = vb + tv.x, vbb = vb + tv.z, vc = vb + tv.y;  // positive-area order
-                if constexpr (SHADE == 4) {  // depth only (shadow maps): no shading
-                    o[h] = PixelOut{0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                } else {
-                    constexpr bool kSpot = (SHADE & 1) != 0, kMat = (SHADE & 2) != 0;
-                    MatTex mt;
-                    if constexpr (kMat) mt = mat_inputs(a, fi.obj_begin + k, mvb, tv);
-                    const int4 A = F.vall(va), B = F.vall(vbb), C = F.vall(vc);
-                    o[h] = shade_pixel<kSpot, kMat>(A.x, A.y, B.x, B.y, C.x, C.y, __int_as_float(A.z),
-                                                    __int_as_float(B.z), __int_as_float(C.z), a.mesh_nrm[mvb + tv.x],
-                                                    a.mesh_nrm[mvb + tv.z],
-                                                    a.mesh_nrm[mvb + tv.y], F.o_R[k], pi, pj, z, cam, S.light,
-                                                    S.light_type, fi.n_lights, F.o_mat[k], S.spot, a.shadow_maps,
-                                                    a.shadow_res, &mt, a.tex_texels, a.tex_info);
+            for (int q = 0; q < 4; ++q) {
+                const bool c = (covq >> q) & 1;
+                const unsigned long long m = __ballot(c);
+                if (c) list[n_cov + lanes_below(m)] = (unsigned char)(lj * kFTileW + li0 + q);
+                n_cov += __popcll(m);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (AUX && a.out_track) {  // tracker: the object slot of each covered pixel's key
+                int sl[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    sl[q] = (covq >> q) & 1 ? (int)((unsigned)vis[lj * kFTileW + li0 + q] >> 16) & 0xff : -1;
+                track_tile(a.out_track + fi.track_base, sl, x0 + li0, y0 + lj);  // frames of at most 256 x 256
+            }
+
+            // shade the covered pixels, lane-compacted (lane takes list[lane + 64 r]), in
+            // passes of (up to) two per lane and put them, over the tile's background, into a
+            // staging slot that a store wave writes out
+            int stg = -1;
+            for (int r0 = 0; r0 * kWave < n_cov; r0 += 2) {
+                PixelOut o[2];
+                unsigned long long kk[2];
+                int sg[2], pl[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    kk[h] = kEmptyKey;
+                    sg[h] = -1;
+                    pl[h] = 0;
+                    const int c = (r0 + h) * kWave + lane;
+                    if (c >= n_cov) continue;
+                    const int p = list[c];
+                    const int pi = x0 + (int)((unsigned)p % kFTileW), pj = y0 + (int)((unsigned)p / kFTileW);
+                    const unsigned long long key = vis[p];
+                    const int tri = (int)(unsigned)(key & 0xffffu), k = (int)(unsigned)((key >> 16) & 0xffu);
+                    const float z = __uint_as_float((unsigned)(key >> 32));
+                    const int4 tv = frame_tri(a, F, k, tri);
+                    const int vb = F.o_vbase[k], mvb = F.o_mvb[k];
+                    const int va = vb + tv.x, vbb = vb + tv.z, vc = vb + tv.y;  // positive-area order
+                    if constexpr (SHADE == 4) {  // depth only (shadow maps): no shading
+                        o[h] = PixelOut{0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                    } else {
+                        constexpr bool kSpot = (SHADE & 1) != 0, kMat = (SHADE & 2) != 0;
+                        MatTex mt;
+                        if constexpr (kMat) mt = mat_inputs(a, fi.obj_begin + k, mvb, tv);
+                        const int4 A = F.vall(va), B = F.vall(vbb), C = F.vall(vc);
+                        o[h] = shade_pixel<kSpot, kMat>(A.x, A.y, B.x, B.y, C.x, C.y, __int_as_float(A.z),
+                                                        __int_as_float(B.z), __int_as_float(C.z), a.mesh_nrm[mvb + tv.x],
+                                                        a.mesh_nrm[mvb + tv.z],
+                                                        a.mesh_nrm[mvb + tv.y], F.o_R[k], pi, pj, z, cam, S.light,
+                                                        S.light_type, fi.n_lights, F.o_mat[k], S.spot, a.shadow_maps,
+                                                        a.shadow_res, &mt, a.tex_texels, a.tex_info);
+                    }
+                    kk[h] = key & ~0xffff0000ull;
+                    sg[h] = F.o_seg[k];
+                    pl[h] = p;
+                    __builtin_amdgcn_sched_barrier(0);  // shade the two pixels one after the other
                 }
-                kk[h] = key & ~0xffff0000ull;
-                sg[h] = F.o_seg[k];
-                pl[h] = p;
-                __builtin_amdgcn_sched_barrier(0);  // shade the two pixels one after the other
+                if (stg < 0) stg = stage_begin(a, S, lane, lj, li0);
+                if (stg < 0) break;  // the workgroup has stopped
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    if (kk[h] != kEmptyKey) stage_pixel(S, stg, pl[h], o[h], sg[h], kk[h]);
             }
             if (stg < 0) stg = stage_begin(a, S, lane, lj, li0);
-            if (stg < 0) break;  // the workgroup has stopped
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-                if (kk[h] != kEmptyKey) stage_pixel(S, stg, pl[h], o[h], sg[h], kk[h]);
+            if (stg < 0) {
+                stopped = true;
+                break;
+            }
+            stage_end(S, stg, f, po, W, H, x0, y0, vec_frame, lane);
         }
-        if (stg < 0) stg = stage_begin(a, S, lane, lj, li0);
-        if (stg < 0) {
-            stopped = true;
-            break;
-        }
-        stage_end(S, stg, f, po, W, H, x0, y0, vec_frame, lane);
-    }
-    return frame_barrier<G>(a, S, gen);  // the frame's LDS is reused by the next frame
+        if (frame_barrier<G>(a, S, gen)) return true;  // the LDS is reused by the next group or frame
+        s0 = s1;
+    } while (s0 < n_busy);
+    return false;
 }
 
 // AUX: the transparency channel and the Tracker records are written (a separate
