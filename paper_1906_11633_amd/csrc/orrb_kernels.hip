@@ -470,14 +470,14 @@ constexpr unsigned kFSpinCap = 1u << 22;  // bound on every wait loop (about 0.3
 
 struct BgFrame {
     long long po;  // pixel offset of the frame
-    int W, H, ntx, vec;
+    int W, H, ntx;
     int n;         // background tiles of the frame
     int f;         // the frame
 };
 
 struct StageInfo {
     long long po;  // pixel offset of the frame
-    int W, H, x0, y0, vec, f;
+    int W, H, x0, y0, f;
 };
 
 // The 8-bit output, encoded by the frame kernel as it writes tiles out: the waves that
@@ -490,11 +490,13 @@ struct PostCache {
 
 ORRB_INLINE bool fused_rgb8(const RenderArgs &a) { return a.out_rgb8 != nullptr; }
 
+typedef unsigned u32_bytes __attribute__((aligned(1)));
+
 // Codes of the lane's four pixels (i .. i + 3, j) of frame f from linear rgb v, stored
-// to the 8-bit planes: one 4-byte store per plane when the group is whole and aligned.
+// to the 8-bit planes: one 4-byte store per plane, at any address, when the group is whole.
 // v == nullptr: four background pixels (rgb 0).
 ORRB_INLINE void store_codes4(const RenderArgs &a, PostCache &pc, int f, int64_t po, int64_t HW, int64_t pix, int i,
-                              int j, const float (*v)[4], bool vec, int n) {
+                              int j, const float (*v)[4], int n) {
     if (pc.f != f) {  // uniform: every lane writes the same frame
         pc.q = post_frame(a, f);
         pc.o_bg = post_grade(pc.q, 0.f, 0.f, 0.f);
@@ -508,8 +510,8 @@ ORRB_INLINE void store_codes4(const RenderArgs &a, PostCache &pc, int f, int64_t
     uint8_t *dst = a.out_rgb8 + 3 * po + pix;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        if (vec) {
-            *reinterpret_cast<unsigned *>(dst + c * HW) = code[c];
+        if (n == 4) {
+            *reinterpret_cast<u32_bytes *>(dst + c * HW) = code[c];
         } else {
 #pragma unroll
             for (int k = 0; k < 4; ++k)
@@ -816,14 +818,17 @@ ORRB_INLINE void frame_append(FrameLds &S, const FrameMem<G> &F, bool keep, unsi
 }
 
 // Four horizontally adjacent pixels of one plane: one 16-byte store when the group is
-// whole and 16-byte aligned, else one store per pixel inside the frame.  Plain stores:
-// the L2 merges a tile's 256-byte row segments with its neighbours' into whole lines,
-// which non-temporal stores forgo.
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
+// whole, else one store per pixel inside the frame.  The store needs the element's
+// alignment only, so rows of any width and planes at any offset take it (768 hand frames of
+// 230 x 230: 502 us, 593 with one store per pixel).  Plain stores: the L2 merges a tile's
+// 256-byte row segments with its neighbours' into whole lines, which non-temporal stores
+// forgo.
+typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned long long u64x2 __attribute__((ext_vector_type(2), aligned(8)));
 
-ORRB_INLINE void store4f(float *p, const float *v, bool vec, int n) {
-    if (vec) {
+ORRB_INLINE void store4f(float *p, const float *v, int n) {
+    if (n == 4) {
         *reinterpret_cast<f32x4 *>(p) = f32x4{v[0], v[1], v[2], v[3]};
     } else {
 #pragma unroll
@@ -832,8 +837,19 @@ ORRB_INLINE void store4f(float *p, const float *v, bool vec, int n) {
     }
 }
 
-ORRB_INLINE void store4i(int *p, const int *v, bool vec, int n) {
-    if (vec) {
+ORRB_INLINE void store4k(unsigned long long *p, const unsigned long long *v, int n) {
+    if (n == 4) {
+        *reinterpret_cast<u64x2 *>(p) = u64x2{v[0], v[1]};
+        *reinterpret_cast<u64x2 *>(p + 2) = u64x2{v[2], v[3]};
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (q < n) p[q] = v[q];
+    }
+}
+
+ORRB_INLINE void store4i(int *p, const int *v, int n) {
+    if (n == 4) {
         *reinterpret_cast<i32x4 *>(p) = i32x4{v[0], v[1], v[2], v[3]};
     } else {
 #pragma unroll
@@ -845,7 +861,7 @@ ORRB_INLINE void store4i(int *p, const int *v, bool vec, int n) {
 // Background (no fragment) for four adjacent pixels: rgb, depth, normal 0, seg and
 // tri_id -1, vis the empty key.
 template <bool AUX>
-ORRB_INLINE void store_background4(const RenderArgs &a, int64_t po, int64_t HW, int64_t pix, bool vec, int n, int f,
+ORRB_INLINE void store_background4(const RenderArgs &a, int64_t po, int64_t HW, int64_t pix, int n, int f,
                                    int i, int j, PostCache &pc) {
     // materialized at each use: hoisted out of the tile loops these constants get
     // spilled, and their reloads would wait for every earlier store of the wave
@@ -856,25 +872,26 @@ ORRB_INLINE void store_background4(const RenderArgs &a, int64_t po, int64_t HW, 
     const float zf[4] = {z, z, z, z};
     const int mi[4] = {m, m, m, m};
     if (a.out_rgb) {
-        store4f(a.out_rgb + 3 * po + pix, zf, vec, n);
-        store4f(a.out_rgb + 3 * po + HW + pix, zf, vec, n);
-        store4f(a.out_rgb + 3 * po + 2 * HW + pix, zf, vec, n);
+        store4f(a.out_rgb + 3 * po + pix, zf, n);
+        store4f(a.out_rgb + 3 * po + HW + pix, zf, n);
+        store4f(a.out_rgb + 3 * po + 2 * HW + pix, zf, n);
     }
-    if (a.out_depth) store4f(a.out_depth + po + pix, zf, vec, n);
+    if (a.out_depth) store4f(a.out_depth + po + pix, zf, n);
     if (a.out_normal) {
-        store4f(a.out_normal + 3 * po + pix, zf, vec, n);
-        store4f(a.out_normal + 3 * po + HW + pix, zf, vec, n);
-        store4f(a.out_normal + 3 * po + 2 * HW + pix, zf, vec, n);
+        store4f(a.out_normal + 3 * po + pix, zf, n);
+        store4f(a.out_normal + 3 * po + HW + pix, zf, n);
+        store4f(a.out_normal + 3 * po + 2 * HW + pix, zf, n);
     }
-    if (a.out_seg) store4i(a.out_seg + po + pix, mi, vec, n);
-    if (a.out_tri) store4i(a.out_tri + po + pix, mi, vec, n);
+    if (a.out_seg) store4i(a.out_seg + po + pix, mi, n);
+    if (a.out_tri) store4i(a.out_tri + po + pix, mi, n);
     if (a.out_vis) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if (q < n) a.out_vis[po + pix + q] = kEmptyKey;
+        const unsigned long long e = (unsigned)m | (unsigned long long)(unsigned)m << 32;
+        static_assert(kEmptyKey == ~0ull, "the empty key is all ones");
+        const unsigned long long ek[4] = {e, e, e, e};
+        store4k(a.out_vis + po + pix, ek, n);
     }
-    if (AUX && a.out_alpha) store4f(a.out_alpha + po + pix, zf, vec, n);
-    if (AUX && fused_rgb8(a)) store_codes4(a, pc, f, po, HW, pix, i, j, nullptr, vec, n);
+    if (AUX && a.out_alpha) store4f(a.out_alpha + po + pix, zf, n);
+    if (AUX && fused_rgb8(a)) store_codes4(a, pc, f, po, HW, pix, i, j, nullptr, n);
 }
 
 // ---- synchronization of the persistent frame workgroup ----
@@ -932,14 +949,6 @@ ORRB_INLINE bool frame_barrier(const RenderArgs &a, FrameLds &S, int &gen) {
     return stop != 0;
 }
 
-// 16-byte stores possible for the frame: width and offset multiples of 4 pixels and
-// every output 16-byte aligned.
-ORRB_INLINE bool frame_vec(const RenderArgs &a, int W, int64_t po) {
-    const uintptr_t align = (uintptr_t)a.out_rgb | (uintptr_t)a.out_depth | (uintptr_t)a.out_normal |
-                            (uintptr_t)a.out_seg | (uintptr_t)a.out_tri | (uintptr_t)a.out_rgb8;
-    return ((W | (int)(po & 3)) & 3) == 0 && (align & 15) == 0;
-}
-
 // Wave 0: hand frame seq's background tiles, order[n_busy .. n_tiles), to the store
 // waves.  The slot is reused only after every store wave has moved past the frame that
 // held it before (so none still takes from it) and all its tiles are written.
@@ -968,7 +977,6 @@ ORRB_INLINE void frame_publish(const RenderArgs &a, FrameLds &S, int seq, int f,
         b.W = W;
         b.H = H;
         b.ntx = ntx;
-        b.vec = frame_vec(a, W, po);
         b.n = n_empty;
         b.f = f;
         S.bg_next[slot] = 0;
@@ -1029,7 +1037,7 @@ ORRB_INLINE void stage_pixel(FrameLds &S, int s, int p, const PixelOut &o, int s
 }
 
 // Hand the filled slot to the store waves, with where the tile goes.
-ORRB_INLINE void stage_end(FrameLds &S, int s, int f, int64_t po, int W, int H, int x0, int y0, bool vec, int lane) {
+ORRB_INLINE void stage_end(FrameLds &S, int s, int f, int64_t po, int W, int H, int x0, int y0, int lane) {
     if (lane == 0) {
         StageInfo &in = S.stage_info[s];
         in.po = po;
@@ -1037,7 +1045,6 @@ ORRB_INLINE void stage_end(FrameLds &S, int s, int f, int64_t po, int W, int H, 
         in.H = H;
         in.x0 = x0;
         in.y0 = y0;
-        in.vec = vec;
         in.f = f;
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -1111,7 +1118,6 @@ ORRB_INLINE void stage_write(const RenderArgs &a, FrameLds &S, int s, int lj, in
     __builtin_amdgcn_wave_barrier();
     if (lane == 0) lds_store(&S.stage_state[s], 0);
     if (n == 0) return;
-    const bool vec = in.vec && n == 4;
     const int64_t HW = (int64_t)in.W * in.H, po = in.po, pix = (int64_t)j * in.W + i0;
     float z[4];
     int seg[4], tri[4];
@@ -1123,34 +1129,30 @@ ORRB_INLINE void stage_write(const RenderArgs &a, FrameLds &S, int s, int lj, in
         seg[q] = __float_as_int(v[6][q]);
     }
     if (a.out_rgb) {
-        store4f(a.out_rgb + 3 * po + pix, v[0], vec, n);
-        store4f(a.out_rgb + 3 * po + HW + pix, v[1], vec, n);
-        store4f(a.out_rgb + 3 * po + 2 * HW + pix, v[2], vec, n);
+        store4f(a.out_rgb + 3 * po + pix, v[0], n);
+        store4f(a.out_rgb + 3 * po + HW + pix, v[1], n);
+        store4f(a.out_rgb + 3 * po + 2 * HW + pix, v[2], n);
     }
-    if (a.out_depth) store4f(a.out_depth + po + pix, z, vec, n);
+    if (a.out_depth) store4f(a.out_depth + po + pix, z, n);
     if (a.out_normal) {
-        store4f(a.out_normal + 3 * po + pix, v[3], vec, n);
-        store4f(a.out_normal + 3 * po + HW + pix, v[4], vec, n);
-        store4f(a.out_normal + 3 * po + 2 * HW + pix, v[5], vec, n);
+        store4f(a.out_normal + 3 * po + pix, v[3], n);
+        store4f(a.out_normal + 3 * po + HW + pix, v[4], n);
+        store4f(a.out_normal + 3 * po + 2 * HW + pix, v[5], n);
     }
-    if (a.out_seg) store4i(a.out_seg + po + pix, seg, vec, n);
-    if (a.out_tri) store4i(a.out_tri + po + pix, tri, vec, n);
-    if (a.out_vis) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if (q < n) a.out_vis[po + pix + q] = key[q];
-    }
+    if (a.out_seg) store4i(a.out_seg + po + pix, seg, n);
+    if (a.out_tri) store4i(a.out_tri + po + pix, tri, n);
+    if (a.out_vis) store4k(a.out_vis + po + pix, key, n);
     if (AUX && a.out_alpha) {
         float al[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) al[q] = key[q] == kEmptyKey ? 0.f : 1.f;
-        store4f(a.out_alpha + po + pix, al, vec, n);
+        store4f(a.out_alpha + po + pix, al, n);
     }
     if (AUX && fused_rgb8(a)) {  // the staged rgb (background 0) encoded on its way out
         const float rv[3][4] = {{v[0][0], v[0][1], v[0][2], v[0][3]},
                                 {v[1][0], v[1][1], v[1][2], v[1][3]},
                                 {v[2][0], v[2][1], v[2][2], v[2][3]}};
-        store_codes4(a, pc, in.f, po, HW, pix, i0, j, rv, vec, n);
+        store_codes4(a, pc, in.f, po, HW, pix, i0, j, rv, n);
     }
 }
 
@@ -1177,8 +1179,7 @@ ORRB_INLINE bool bg_write_next(const RenderArgs &a, FrameLds &S, int slot, int l
     const int j = y0 + lj, i0 = x0 + li0;
     const int n_in = j <= y1 ? max(0, min(4, x1 - i0 + 1)) : 0;
     if (n_in > 0)
-        store_background4<AUX>(a, b.po, (int64_t)b.W * b.H, (int64_t)j * b.W + i0, b.vec && n_in == 4, n_in, b.f, i0,
-                               j, pc);
+        store_background4<AUX>(a, b.po, (int64_t)b.W * b.H, (int64_t)j * b.W + i0, n_in, b.f, i0, j, pc);
     return true;
 }
 
@@ -1444,7 +1445,6 @@ ORRB_INLINE bool frame_render(const RenderArgs &a, FrameLds &S, int item, int se
     const int n_busy = S.misc[4], n_surv = S.misc[3];
     const CamF cam = frame_camera(a, f);
     const int64_t HW = (int64_t)W * H, po = fi.pixel_offset;
-    const bool vec_frame = frame_vec(a, W, po);
     const bool scan_all = overflow && S.misc[2] > n_busy * (F.bin_max / kFCW);
     int s0 = 0;
     do {
@@ -1659,7 +1659,7 @@ ORRB_INLINE bool frame_render(const RenderArgs &a, FrameLds &S, int item, int se
                 stopped = true;
                 break;
             }
-            stage_end(S, stg, f, po, W, H, x0, y0, vec_frame, lane);
+            stage_end(S, stg, f, po, W, H, x0, y0, lane);
         }
         if (frame_barrier<G>(a, S, gen)) return true;  // the LDS is reused by the next group or frame
         s0 = s1;
