@@ -61,6 +61,7 @@ struct RenderArgs {
     unsigned long long *p_account;   // per frame: sums of its patches (patch_account), or null
     const int32_t *light_type;
     int32_t n_vitems, n_titems, n_fitems;
+    int32_t v_wave;         // k_vertex: a wave per item (1) or a workgroup (0)
     int32_t f_grid;         // frame kernel grid: workgroup b starts with fitems[b]
     int32_t f_dynamic;      // 0: workgroup b then renders fitems[b + k f_grid]; 1: it claims
                             // fitems[f_grid + queue[kFrameQueue]++] after each frame

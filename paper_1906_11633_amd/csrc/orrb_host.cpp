@@ -188,6 +188,7 @@ struct orrb_layout {
     std::vector<FrameInfo> frames;
     std::vector<ObjInfo> objs;
     std::vector<int64_t> scene_verts, scene_tris;
+    int32_t max_obj_verts = 0;  // of any object
     // per frame: 1 scene fits in LDS (frame and patch kernel), 2 the frame kernel's global
     // scratch (and the patch kernel's workspace form), 3 only the latter, 0 none
     std::vector<uint8_t> fits;
@@ -305,6 +306,14 @@ static bool valid_tuning(const orrb_tuning &t) {
 static double frame_cost(const orrb_layout *L, int32_t f, bool scratch) {
     const FrameInfo &fi = L->frames[f];
     return (double)L->scene_tris[fi.scene] * (scratch ? 1.5 : 1.0) + 0.25 * (double)fi.width * fi.height;
+}
+
+// Whether k_vertex gives each of n items a wave instead of a workgroup: with eight items a CU
+// there are waves enough (72 frames of 28 objects: 31 us either way, 24 frames: 24 and 26 with
+// a wave), and objects of up to 1,024 vertices keep a wave's loop short.
+static int32_t vertex_by_wave(const orrb_layout *L, int64_t n) {
+    const int64_t n_cu = L->ctx ? L->ctx->n_cu : 256;
+    return n >= 8 * n_cu && L->max_obj_verts <= 1024;
 }
 
 // Schedule of the frame kernel's persistent grid (min(frames, CUs) workgroups).  A
@@ -1028,6 +1037,7 @@ orrb_status orrb_layout_create(orrb_context *ctx, const orrb_layout_desc *d, orr
             ob.scene_vbase = (int32_t)vb;
             ob.scene_tbase = (int32_t)tb;
             ob.mesh = m;
+            L->max_obj_verts = std::max(L->max_obj_verts, ob.n_verts);
             vb += ob.n_verts;
             tb += ob.n_tris;
             if (vb > 0x7fffffff || tb > ORRB_MAX_SCENE_TRIANGLES) {
@@ -1256,6 +1266,7 @@ orrb_status orrb::render_impl(orrb_context *ctx, const orrb_layout *L, const orr
     a.f_grid = L->f_grid;
     a.f_dynamic = L->f_dynamic;
     a.n_vitems = (int32_t)L->vitems.size();
+    a.v_wave = vertex_by_wave(L, a.n_vitems);
     a.n_titems = (int32_t)L->titems.size();
     a.tile_w = L->tuning.tile_w;
     a.tile_h = L->tuning.tile_h;
@@ -1430,6 +1441,7 @@ orrb_status orrb_shade_backward(orrb_context *ctx, const orrb_layout *L, const o
     g.r.frames = L->gtab.at<FrameInfo>(L->g_frames_all);
     g.r.vitems = L->gtab.at<int2>(L->g_vitems_all);
     g.r.n_vitems = (int32_t)L->vitems_all.size();
+    g.r.v_wave = vertex_by_wave(L, g.r.n_vitems);
     g.r.vtx_pos = (int4 *)(ws + w.vtx_pos);
     g.r.obj_rot = (float4 *)(ws + w.obj_rot);
     g.r.obj_bbox = (int4 *)(ws + w.obj_bbox);

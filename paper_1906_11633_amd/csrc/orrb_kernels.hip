@@ -21,7 +21,7 @@
 // auxiliary-output kernels a compute wave out of busy tiles also writes background.
 //
 // Tiled path (k_vertex + k_raster_shade), for any scene size:
-//   k_vertex        one workgroup per (frame, object): FP64 transform and snap into a
+//   k_vertex        one workgroup or wave per (frame, object): FP64 transform and snap into a
 //                   global workspace, the object's covered pixel-centre range and its
 //                   view rotation;
 //   k_raster_shade  one workgroup per (frame, screen tile): cull objects by their
@@ -44,38 +44,51 @@ namespace orrb {
 // tiled path: k_vertex
 // ------------------------------------------------------------------------------------
 
+// Latency bound: an object of a few hundred vertices is one pass of a workgroup behind a chain
+// of dependent loads and the FP64 composition of its matrix.  WAVE: each wave takes an object
+// of its own, so a workgroup runs four such chains at once and the composition is done by one
+// wave an object, not four.  192 hand frames (5,376 objects of 250 vertices on average) of
+// 200 x 200, adjoint: 91 us with a workgroup an object, 87 with a wave; 768 of 64 x 64: 106 and 84.
+template <bool WAVE>
 __global__ __launch_bounds__(kBlock) void k_vertex(RenderArgs a) {
     if (blockIdx.x == 0 && threadIdx.x == 0) *a.queue = 0u;  // persistent raster counter
-    if ((int)blockIdx.x >= a.n_vitems) return;
-    __shared__ double M[12];
+    constexpr int kGroup = WAVE ? kWave : kBlock, kItems = kBlock / kGroup;
+    __shared__ double M_[kItems][12];
     __shared__ int red[4][kBlock / kWave];
-    const int2 it = a.vitems[blockIdx.x];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int sub = WAVE ? wave : 0, t = WAVE ? lane_id() : (int)threadIdx.x;
+    const int item = blockIdx.x * kItems + sub;
+    if (item >= a.n_vitems) return;
+    double *M = M_[sub];
+    const int2 it = a.vitems[item];
     const int f = it.x;
     const FrameInfo fi = a.frames[f];
     const int o = fi.obj_begin + it.y;
     const int oi = fi.oi_base + it.y;
-    if (threadIdx.x < 12) M[threadIdx.x] = compose_entry(a.view + 12 * (int64_t)f, a.pose + 12 * (int64_t)o, threadIdx.x);
-    __syncthreads();
+    if (t < 12) M[t] = compose_entry(a.view + 12 * (int64_t)f, a.pose + 12 * (int64_t)o, t);
+    if constexpr (WAVE) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        __syncthreads();
+    }
     const float *K = a.intr + 4 * (int64_t)f;
     const double fx = K[0], fy = K[1], cx = K[2], cy = K[3], nearp = a.near_plane[f];
-    if (a.out_track && threadIdx.x == 0)  // hidden objects too: their origin is still reported
+    if (a.out_track && t == 0)  // hidden objects too: their origin is still reported
         track_init(a.out_track + fi.track_base + it.y, M[3], M[7], M[11], fx, fy, cx, cy);
     if (!a.visible[o]) {
-        if (threadIdx.x == 0) a.obj_bbox[oi] = make_int4(1, 1, 0, 0);
+        if (t == 0) a.obj_bbox[oi] = make_int4(1, 1, 0, 0);
         return;
     }
     const ObjInfo ob = a.objs[o];
-    if (threadIdx.x < 3) {
-        const int r = threadIdx.x;
-        a.obj_rot[3 * (int64_t)oi + r] = make_float4((float)M[4 * r + 0], (float)M[4 * r + 1], (float)M[4 * r + 2], 0.f);
-    }
+    if (t < 3) a.obj_rot[3 * (int64_t)oi + t] = make_float4((float)M[4 * t + 0], (float)M[4 * t + 1], (float)M[4 * t + 2], 0.f);
     double Mr[12];
 #pragma unroll
     for (int k = 0; k < 12; ++k) Mr[k] = M[k];
     int xmin = 0x7fffffff, ymin = 0x7fffffff, xmax = -0x7fffffff, ymax = -0x7fffffff;
     const int64_t vb = fi.vbase + ob.scene_vbase;
     unsigned n_near = 0, n_guard = 0;
-    for (int v = threadIdx.x; v < ob.n_verts; v += kBlock) {
+    for (int v = t; v < ob.n_verts; v += kGroup) {
         const Snapped s = snap_vertex(Mr, a.mesh_pos[ob.mesh_vbegin + v], fx, fy, cx, cy, nearp);
         a.vtx_pos[vb + v] = make_int4(s.X, s.Y, __float_as_int(s.iw), s.valid);
         n_near += s.cull == 1;
@@ -96,21 +109,24 @@ __global__ __launch_bounds__(kBlock) void k_vertex(RenderArgs a) {
         xmax = max(xmax, __shfl_xor(xmax, off));
         ymax = max(ymax, __shfl_xor(ymax, off));
     }
-    const int wave = threadIdx.x / kWave;
-    if (lane_id() == 0) {
-        red[0][wave] = xmin;
-        red[1][wave] = ymin;
-        red[2][wave] = xmax;
-        red[3][wave] = ymax;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < kBlock / kWave; ++w) {
-            xmin = min(xmin, red[0][w]);
-            ymin = min(ymin, red[1][w]);
-            xmax = max(xmax, red[2][w]);
-            ymax = max(ymax, red[3][w]);
+    if constexpr (!WAVE) {
+        if (lane_id() == 0) {
+            red[0][wave] = xmin;
+            red[1][wave] = ymin;
+            red[2][wave] = xmax;
+            red[3][wave] = ymax;
         }
+        __syncthreads();
+        if (t == 0) {
+            for (int w = 1; w < kBlock / kWave; ++w) {
+                xmin = min(xmin, red[0][w]);
+                ymin = min(ymin, red[1][w]);
+                xmax = max(xmax, red[2][w]);
+                ymax = max(ymax, red[3][w]);
+            }
+        }
+    }
+    if (t == 0) {
         int4 bb = make_int4(1, 1, 0, 0);
         if (xmin <= xmax) {
             bb.x = max(ceil256(xmin - 128), 0);
@@ -1735,7 +1751,11 @@ hipError_t launch_shadow_cams(const int32_t *spot_light, int n_spot, const float
 }
 
 hipError_t launch_vertex(const RenderArgs &a, hipStream_t stream) {
-    hipLaunchKernelGGL(k_vertex, dim3(a.n_vitems > 0 ? a.n_vitems : 1), dim3(kBlock), 0, stream, a);
+    constexpr int kWaves = kBlock / kWave;
+    if (a.v_wave)
+        hipLaunchKernelGGL(k_vertex<true>, dim3((a.n_vitems + kWaves - 1) / kWaves), dim3(kBlock), 0, stream, a);
+    else
+        hipLaunchKernelGGL(k_vertex<false>, dim3(a.n_vitems > 0 ? a.n_vitems : 1), dim3(kBlock), 0, stream, a);
     return hipGetLastError();
 }
 
