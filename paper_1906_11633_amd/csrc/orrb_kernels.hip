@@ -1810,8 +1810,9 @@ hipError_t launch_frame(const RenderArgs &a, hipStream_t stream, int n_cu) {
     const bool aux = a.out_alpha || a.out_track || a.out_rgb8, mixed = a.fscratch != nullptr;
     const dim3 g(grid), b(kFT);
 #define ORRB_FRAME(AUX_, MIXED_, SHADE_) hipLaunchKernelGGL((k_frame<AUX_, MIXED_, SHADE_>), g, b, 0, stream, a)
-    switch (a.shade_mode) {
-        case 4:  // depth only (shadow maps); no auxiliary outputs
+    // depth only (shadow maps) has no auxiliary variant: with alpha or Tracker records the plain one
+    switch (a.shade_mode == 4 && aux ? 0 : a.shade_mode) {
+        case 4:
             if (mixed) ORRB_FRAME(false, true, 4); else ORRB_FRAME(false, false, 4);
             break;
         case 1:  // spot lights with shadow maps
