@@ -27,7 +27,7 @@ struct FrameInfo {
     int32_t oi_base;            // first (frame, object) instance
     int32_t light_begin, n_lights;
     int32_t track_base;         // first tracker record (frame, object) of the frame
-    int32_t mode;               // frame kernel: 0 scene data in LDS, 1 in the global frame scratch
+    int32_t mode;               // scene data: 0 in LDS, 1 in the global frame scratch, 2 k_vertex's records (patches)
     int32_t pad0;
 };
 
@@ -48,6 +48,11 @@ struct PatchItem {
     int32_t parts;
 };
 
+// The frame kernel's limits for one kind of scene, for a call's counters (bin_max 0: not counted).
+struct PatchLimits {
+    int32_t bin_max, surv_max;
+};
+
 struct RenderArgs {
     // layout tables
     const FrameInfo *frames;
@@ -57,7 +62,8 @@ struct RenderArgs {
     const int32_t *fitems;  // frames rendered by k_frame
     const PatchItem *pitems;  // rectangles of frames rendered by k_patch
     int32_t n_pitems;
-    int32_t p_side, p_bin_max, p_surv_max;  // the frame kernel's limits, for the call's counters
+    int32_t p_side;            // the frame kernel's largest frame
+    PatchLimits p_limits[2];   // of scenes held in LDS and of larger ones
     unsigned long long *p_account;   // per frame: sums of its patches (patch_account), or null
     const int32_t *light_type;
     int32_t n_vitems, n_titems, n_fitems;
@@ -175,7 +181,7 @@ hipError_t launch_shadow_cams(const int32_t *spot_light, int n_spot, const float
 hipError_t launch_validate(const RenderArgs &a, const float *post, int n_obj, int n_lights, int n_frames,
                            uint32_t *stats, hipStream_t stream);
 hipError_t read_wait_timeouts(unsigned int *out);  // frame-kernel waits that hit their bound
-hipError_t launch_patch(const RenderArgs &a, bool global, hipStream_t stream);
+hipError_t launch_patch(const RenderArgs &a, int kind, hipStream_t stream);
 bool frame_fits(int64_t n_verts, int n_obj, int64_t n_tris);       // scenes held in LDS
 bool frame_fits_global(int64_t n_verts, int n_obj, int64_t n_tris);  // in the frame kernel's scratch
 int frame_max_side();                                                // frames up to this wide and high

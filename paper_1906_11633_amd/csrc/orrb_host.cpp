@@ -197,14 +197,15 @@ struct orrb_layout {
     int64_t gp_tris = 0;  // most triangles of a larger scene rendered as patches
     std::vector<int2> vitems, titems;
     std::vector<int32_t> fitems;  // frame-kernel schedule (see schedule_frames)
-    std::vector<PatchItem> pitems, gpitems;  // patches of LDS-held and of larger scenes (see schedule_patches)
+    std::vector<PatchItem> pitems;  // patches of LDS-held and of larger scenes (see schedule_patches)
+    int64_t gp_items = 0;           // of these, of larger scenes
     int64_t p_frames = 0, gp_frames = 0;     // frames rendered as such patches
     int64_t f_frames = 0;          // frames on the frame kernel
     int32_t f_grid = 0;            // its persistent grid
     int32_t f_dynamic = 0;         // 1: frames claimed from a counter (uneven batch)
     std::vector<int32_t> light_type;
     Packed tab;  // frames, objs, vitems, titems, fitems, pitems, light_type, spot tables
-    size_t o_pitems = 0, o_gpitems = 0;
+    size_t o_pitems = 0;
     size_t o_frames = 0, o_objs = 0, o_vitems = 0, o_titems = 0, o_fitems = 0, o_light_type = 0;
     // spot lights (type 2) with shadow maps: one N x N depth frame per spot light, from
     // its shadow camera, rendered by a sub-layout before the frames themselves
@@ -453,23 +454,27 @@ static void choose_patches(const orrb_layout *L, std::vector<int32_t> &frames, b
     patched.insert(patched.end(), rest.begin() + keep, rest.end());
 }
 
-// The patches of frames `patched`: the CUs are shared out by estimated work.
-static void schedule_patches(const orrb_layout *L, const std::vector<int32_t> &patched, bool global,
-                             std::vector<PatchItem> &items) {
+// The patches of the frames `patched` (scenes held in LDS) and `gpatched` (larger ones): the CUs
+// are shared out by estimated work.
+static void schedule_patches(orrb_layout *L, const std::vector<int32_t> &patched, const std::vector<int32_t> &gpatched) {
     const int64_t n_cu = L->ctx ? L->ctx->n_cu : 256;
-    const int cap = patch_max_pixels(global);
+    std::vector<PatchItem> &items = L->pitems;
     items.clear();
     double total = 0.0;
-    bool uniform = !patched.empty();
+    bool uniform = gpatched.empty() && !patched.empty();
     for (int32_t f : patched) {
         total += frame_cost(L, f, false);
         uniform = uniform && frame_cost(L, f, false) == frame_cost(L, patched[0], false);
     }
+    for (int32_t f : gpatched) total += frame_cost(L, f, true);
     int64_t pixels = 0;
     for (const FrameInfo &fi : L->frames) pixels += (int64_t)fi.width * fi.height;
+    for (int32_t f : gpatched)
+        cut_frame(L->frames[f], f, patch_max_pixels(true), (double)n_cu * frame_cost(L, f, true) / total, false, false, items);
+    L->gp_items = (int64_t)items.size();
     for (int32_t f : patched)
-        cut_frame(L->frames[f], f, cap, (double)n_cu * frame_cost(L, f, false) / total,
-                  !global && uniform && L->scene_tris[L->frames[f].scene] >= 2048, pixels <= 8 << 20, items);
+        cut_frame(L->frames[f], f, patch_max_pixels(false), (double)n_cu * frame_cost(L, f, false) / total,
+                  uniform && L->scene_tris[L->frames[f].scene] >= 2048, pixels <= 8 << 20, items);
     // The middle of a frame usually shows the most: patches nearest to their frame's centre
     // first, so that the last ones to run are light, and the same patch of consecutive
     // frames on consecutive XCDs (in frame order, eight patches a frame put all the middle
@@ -498,7 +503,7 @@ static int64_t render_kernels(const orrb_layout *L) {
     if (!L->vitems.empty() || !L->titems.empty()) n += 1;
     if (!L->titems.empty()) n += 1;
     if (!L->fitems.empty()) n += 1 + L->f_dynamic;
-    n += !L->pitems.empty() + !L->gpitems.empty();
+    n += !L->pitems.empty();
     return n;
 }
 
@@ -553,7 +558,7 @@ static CallWs call_ws(const orrb_layout *L) { return call_ws(L, L->shadow ? ws_l
 // they become patches).  The frame kernel takes as long as its costliest frame or, with many
 // frames, as the work over the CUs; the patches cost about 1.3 times as much work (and a
 // vertex kernel) but spread over the chip.  Measured (one MI355X, us, frame kernel / patches):
-// 24 uneven frames 175 / 54, 192: 365 / 172, 384: 382 / 273, 768 (work over the CUs equal to
+// 24 uneven frames 175 / 47, 192: 365 / 146, 384: 382 / 256, 768 (work over the CUs equal to
 // the costliest frame): 514 / 516, 1,536: 713 / 890, 3,072: 1,399 / 1,694.
 static bool frame_scratch_pays(const orrb_layout *L) {
     double sum = 0.0, most = 0.0;
@@ -607,6 +612,7 @@ static void build_items(orrb_layout *L) {
         oi += fi.n_obj;
         if (path != 1 && L->fits[f] != 0) {
             gpatched.push_back((int32_t)f);
+            fi.mode = 2;
             L->gp_tris = std::max<int64_t>(L->gp_tris, L->scene_tris[fi.scene]);
             continue;
         }
@@ -617,8 +623,7 @@ static void build_items(orrb_layout *L) {
     L->tiled_object_instances = oi;
     choose_patches(L, L->fitems, L->gframes > 0, patched);
     schedule_frames(L);
-    schedule_patches(L, patched, false, L->pitems);
-    schedule_patches(L, gpatched, true, L->gpitems);
+    schedule_patches(L, patched, gpatched);
     L->p_frames = (int64_t)patched.size();
     L->gp_frames = (int64_t)gpatched.size();
 }
@@ -718,7 +723,6 @@ static orrb_status upload_layout(orrb_layout *L) {
     L->o_titems = P.add(L->titems);
     L->o_fitems = P.add(L->fitems);
     L->o_pitems = P.add(L->pitems);
-    L->o_gpitems = P.add(L->gpitems);
     L->o_light_type = P.add(L->light_type);
     if (L->n_spot > 0) {
         L->o_spot_slot = P.add(L->spot_slot);
@@ -1179,7 +1183,7 @@ orrb_status orrb_layout_info_get(const orrb_layout *L, orrb_layout_info *info) {
     info->triangle_instances = L->triangle_instances;
     // larger scenes' patches count as the tiled path's under path 0, as the frame path's under 2
     const bool gp_tiled = L->tuning.path != 2;
-    info->tile_items = (int64_t)(L->titems.size() + (gp_tiled ? L->gpitems.size() : 0));
+    info->tile_items = (int64_t)(L->titems.size() + (gp_tiled ? L->gp_items : 0));
     info->frame_path_frames = L->f_frames + L->p_frames + (gp_tiled ? 0 : L->gp_frames);
     info->workspace_bytes = call_ws(L).total;
     info->workspace_bytes_any = ws_bytes_any(L);
@@ -1323,7 +1327,7 @@ orrb_status orrb::render_impl(orrb_context *ctx, const orrb_layout *L, const orr
     for (int k = 0; k < 3 && e == hipSuccess; ++k) {
         if (k == 0 && a.n_titems == 0 && a.n_vitems == 0) continue;  // no frame needs k_vertex
         if (k == 1 && a.n_titems == 0) continue;
-        if (k == 2 && a.n_fitems == 0 && L->pitems.empty() && L->gpitems.empty()) continue;
+        if (k == 2 && a.n_fitems == 0 && L->pitems.empty()) continue;
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (T.enabled && timing) {
             e0 = T.get();
@@ -1332,20 +1336,18 @@ orrb_status orrb::render_impl(orrb_context *ctx, const orrb_layout *L, const orr
         }
         if (e == hipSuccess)
             e = k == 0 ? launch_vertex(a, st) : k == 1 ? launch_raster(a, st, ctx->n_cu) : launch_frame(a, st, ctx->n_cu);
-        for (int g = 0; k == 2 && g < 2 && e == hipSuccess; ++g) {  // patches of LDS-held, then of larger scenes
-            const std::vector<PatchItem> &items = g ? L->gpitems : L->pitems;
-            RenderArgs b = a;
-            b.pitems = L->tab.at<PatchItem>(g ? L->o_gpitems : L->o_pitems);
-            b.n_pitems = (int32_t)items.size();
-            b.p_side = frame_max_side();
-            frame_limits(&b.p_bin_max, &b.p_surv_max);
-            if (g) {  // the frame kernel's global scratch (path 2) would have had these limits
+        if (k == 2 && e == hipSuccess) {
+            a.pitems = L->tab.at<PatchItem>(L->o_pitems);
+            a.n_pitems = (int32_t)L->pitems.size();
+            a.p_side = frame_max_side();
+            frame_limits(&a.p_limits[0].bin_max, &a.p_limits[0].surv_max);
+            if (L->tuning.path == 2) {  // the frame kernel's global scratch would have had these limits
                 const FrameScratch fs = frame_scratch(1, 1, 1, L->gp_tris, L->tuning.bin_cap, 1);
-                b.p_bin_max = (int32_t)std::min<int64_t>(fs.bins, 0x7fffffff);
-                b.p_surv_max = (int32_t)fs.surv;
+                a.p_limits[1].bin_max = (int32_t)std::min<int64_t>(fs.bins, 0x7fffffff);
+                a.p_limits[1].surv_max = (int32_t)fs.surv;
             }
-            if (out->stats && (!g || L->tuning.path == 2)) b.p_account = (unsigned long long *)(ws + w.account);
-            e = launch_patch(b, g != 0, st);
+            if (out->stats && (L->p_frames > 0 || L->tuning.path == 2)) a.p_account = (unsigned long long *)(ws + w.account);
+            e = launch_patch(a, L->p_frames == 0 ? 1 : L->gp_frames == 0 ? 0 : 2, st);
         }
         if (T.enabled && timing && e0 && e1 && e == hipSuccess) {
             e = hipEventRecord(e1, st);

@@ -234,19 +234,20 @@ ORRB_INLINE int patch_setup(int4 A, int4 B, int4 C, int px0, int py0, int pw, in
 // whole.  A patch adds the triangles whose first pixel it holds (so each counts once) and
 // their 64 x 4 tiles to its frame's sums; the frame's last patch compares them with the
 // frame kernel's limits.
-ORRB_INLINE void patch_account(const RenderArgs &a, const PatchItem &it, unsigned entries, unsigned survivors) {
+ORRB_INLINE void patch_account(const RenderArgs &a, const PatchItem &it, unsigned entries, unsigned survivors,
+                               const PatchLimits &limits) {
     const unsigned long long add = (1ull << 52) | ((unsigned long long)survivors << 32) | entries;
     const unsigned long long sum = atomicAdd(a.p_account + it.frame, add) + add;
     if ((int)(sum >> 52) != it.parts) return;
-    const bool overflow = (unsigned)sum > (unsigned)a.p_bin_max;
+    const bool overflow = (unsigned)sum > (unsigned)limits.bin_max;
     stat_add(a, ORRB_STAT_BIN_OVERFLOW, overflow ? 1u : 0u);
-    stat_add(a, ORRB_STAT_SURVIVOR_RESETUP, !overflow && ((sum >> 32) & 0xfffff) > (unsigned)a.p_surv_max ? 1u : 0u);
+    stat_add(a, ORRB_STAT_SURVIVOR_RESETUP, !overflow && ((sum >> 32) & 0xfffff) > (unsigned)limits.surv_max ? 1u : 0u);
 }
 
 template <bool AUX, bool G, int SHADE>
-__global__ __launch_bounds__(kPT) void k_patch(RenderArgs a) {
-    __shared__ PatchLds<G> S;
-    const PatchItem it = a.pitems[blockIdx.x];
+ORRB_INLINE void patch_render(const RenderArgs &a, PatchLds<G> &S, const PatchItem it) {
+    const PatchLimits limits = a.p_limits[G];
+    const bool account = a.p_account && limits.bin_max > 0;
     const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid) / kWave;
     const int f = it.frame;
     const FrameInfo fi = a.frames[f];
@@ -423,7 +424,7 @@ __global__ __launch_bounds__(kPT) void k_patch(RenderArgs a) {
             const int n = t >= 0 ? patch_setup(verts.get(base + tri.x), verts.get(base + tri.z), verts.get(base + tri.y),
                                                px0, py0, pw, ph, T)
                                  : 0;
-            if (a.p_account && n > 0 && fi.width <= a.p_side && fi.height <= a.p_side) {
+            if (account && n > 0 && fi.width <= a.p_side && fi.height <= a.p_side) {
                 const int xmin = min(T.xa, min(T.xb, T.xc)), xmax = max(T.xa, max(T.xb, T.xc));
                 const int ymin = min(T.ya, min(T.yb, T.yc)), ymax = max(T.ya, max(T.yb, T.yc));
                 const int i0 = max(ceil256(xmin - 128), 0), j0 = max(ceil256(ymin - 128), 0);
@@ -466,12 +467,12 @@ __global__ __launch_bounds__(kPT) void k_patch(RenderArgs a) {
         if (first >= n_big) break;
         raster(first + (lane >> 4), n_big, S.big, lane & 3, (lane >> 2) & 3, 2);
     }
-    if (a.p_account) {
+    if (account) {
         if (entries) atomicAdd(&S.account[0], entries);
         if (survivors) atomicAdd(&S.account[1], survivors);
     }
     __syncthreads();
-    if (a.p_account && tid == 0) patch_account(a, it, S.account[0], S.account[1]);
+    if (account && tid == 0) patch_account(a, it, S.account[0], S.account[1], limits);
 
     // ---- 4: shade and store ----
     const CamF cam = frame_camera(a, f);
@@ -578,6 +579,27 @@ __global__ __launch_bounds__(kPT) void k_patch(RenderArgs a) {
     }
 }
 
+// KIND: every patch's scene is held in LDS (0) or larger (1), or either (2, FrameInfo::mode 2):
+// one launch for both halves of a mixed batch, whose patches share out the CUs between them
+// (60 mixed frames: 88 us
+// in two launches, 73 in one; 231: 197 and 178).
+template <bool AUX, int KIND, int SHADE>
+__global__ __launch_bounds__(kPT) void k_patch(RenderArgs a) {
+    __shared__ union {
+        PatchLds<KIND == 1> one;
+        PatchLds<KIND != 0> larger;
+    } S;
+    const PatchItem it = a.pitems[blockIdx.x];
+    if constexpr (KIND != 2) {
+        patch_render<AUX, KIND == 1, SHADE>(a, S.one, it);
+    } else {
+        if (a.frames[it.frame].mode == 2)
+            patch_render<AUX, true, SHADE>(a, S.larger, it);
+        else
+            patch_render<AUX, false, SHADE>(a, S.one, it);
+    }
+}
+
 // What must hold before the patches start: their frames' counter sums at 0 and Tracker
 // records empty (patches add to them in any order).  One workgroup per patch; each frame's
 // first patch does the frame's.
@@ -594,20 +616,24 @@ __global__ __launch_bounds__(kWave) void k_patch_prepare(RenderArgs a) {
                K[0], K[1], K[2], K[3]);
 }
 
-// a.pitems: the patches of scenes held in LDS, or (global) of larger ones, whose vertices
-// k_vertex has written (it also starts their Tracker records).
-hipError_t launch_patch(const RenderArgs &a, bool global, hipStream_t stream) {
+// a.pitems: the patches of scenes held in LDS (kind 0), of larger ones, whose vertices
+// k_vertex has written (1; it also starts their Tracker records), or of both (2).
+hipError_t launch_patch(const RenderArgs &a, int kind, hipStream_t stream) {
     if (a.n_pitems <= 0) return hipSuccess;
-    if (a.p_account || (a.out_track && !global))
+    if (a.p_account || (a.out_track && kind != 1))
         hipLaunchKernelGGL(k_patch_prepare, dim3(a.n_pitems), dim3(kWave), 0, stream, a);
     const bool aux = a.out_alpha || a.out_track || a.out_rgb8;
     const dim3 g(a.n_pitems), b(kPT);
+#define ORRB_PATCH_KIND(KIND_, SHADE_)                                                               \
+    do {                                                                                             \
+        if (aux) hipLaunchKernelGGL((k_patch<true, KIND_, SHADE_>), g, b, 0, stream, a);             \
+        else hipLaunchKernelGGL((k_patch<false, KIND_, SHADE_>), g, b, 0, stream, a);                \
+    } while (0)
 #define ORRB_PATCH(SHADE_)                                                                           \
     do {                                                                                             \
-        if (global && aux) hipLaunchKernelGGL((k_patch<true, true, SHADE_>), g, b, 0, stream, a);    \
-        else if (global) hipLaunchKernelGGL((k_patch<false, true, SHADE_>), g, b, 0, stream, a);     \
-        else if (aux) hipLaunchKernelGGL((k_patch<true, false, SHADE_>), g, b, 0, stream, a);        \
-        else hipLaunchKernelGGL((k_patch<false, false, SHADE_>), g, b, 0, stream, a);                \
+        if (kind == 2) ORRB_PATCH_KIND(2, SHADE_);                                                   \
+        else if (kind == 1) ORRB_PATCH_KIND(1, SHADE_);                                              \
+        else ORRB_PATCH_KIND(0, SHADE_);                                                             \
     } while (0)
     switch (a.shade_mode) {
         case 4: ORRB_PATCH(4); break;
@@ -617,6 +643,7 @@ hipError_t launch_patch(const RenderArgs &a, bool global, hipStream_t stream) {
         default: ORRB_PATCH(0);
     }
 #undef ORRB_PATCH
+#undef ORRB_PATCH_KIND
     return hipGetLastError();
 }
 
