@@ -113,7 +113,7 @@ ORRB_INLINE int grad_item(const GradArgs &g, int b) {
 // pixel and light) and the FP64 sums over the wave.  Working through the list of covered
 // pixels (hand scenes cover about a quarter of a busy frame's pixels) keeps the lanes
 // full, and sums of four values fold together; 192 frames of 200 x 200: 241 us with one
-// pass per 64 tile pixels and a separate sum per value, 74 us so.
+// pass per 64 tile pixels and a separate sum per value, 66 us so.
 __global__ __launch_bounds__(kBlock) void k_grad_tile(GradArgs g) {
     __shared__ GradLds S;
     const RenderArgs &a = g.r;
