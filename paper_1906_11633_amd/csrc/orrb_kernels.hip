@@ -1527,8 +1527,10 @@ ORRB_INLINE bool frame_render(const RenderArgs &a, FrameLds &S, int item, int se
             if (lane == 0) slot = atomicAdd(&S.misc[0], 1);
             slot = __builtin_amdgcn_readlane(slot, 0);
             if (slot >= s1) {
-                if (slot == n_busy) frame_next(a, S, item, seq, lane);
-                if (AUX && s1 == n_busy) frame_bg_help<AUX>(a, S, seq, lj, li0, lane);
+                if (s1 == n_busy) {  // the last group (in an earlier one, too, a wave may draw slot n_busy)
+                    if (slot == n_busy) frame_next(a, S, item, seq, lane);
+                    if constexpr (AUX) frame_bg_help<AUX>(a, S, seq, lj, li0, lane);
+                }
                 break;
             }
             const int t = S.order[slot];
