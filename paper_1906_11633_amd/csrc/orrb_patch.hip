@@ -31,6 +31,8 @@
 // 27 / 9.5, 6 hand frames of 128 x 128 68 / 16, 48 of 200 x 200 118 / 49; 2 of 1024 x 768
 // (tiled path before) 113 / 30.  Larger scenes (G), 24 / 192 / 384 uneven frames: tiled path
 // 132 / 387 / 683, frame kernel with global scratch 175 / 365 / 382, patches 54 / 172 / 276.
+#include <cstddef>
+
 #include "orrb_post.h"
 
 namespace orrb {
@@ -53,7 +55,7 @@ struct PatchLds {
     float iw[G ? 1 : kPVMax];
     double M[G ? 1 : kPOMax][12];
     unsigned char keep[G ? 1 : kPOMax];
-    unsigned long long vis[G ? kPGPixels : kPPixels];  // (depth bits << 32) | object << 16 | scene triangle
+    alignas(16) unsigned long long vis[G ? kPGPixels : kPPixels];  // (depth bits << 32) | object << 16 | scene triangle
     float R[kObj][9];
     Material mat[kObj];
     int tbase[kObj], mtb[kObj], mvb[kObj], vbase[kObj], seg[kObj];
@@ -67,6 +69,8 @@ struct PatchLds {
     unsigned account[2];  // bin entries and survivors the frame kernel would count
 };
 static_assert(sizeof(PatchLds<false>) <= 160 * 1024 && sizeof(PatchLds<true>) <= 160 * 1024, "patch LDS exceeds 160 KB");
+static_assert(offsetof(PatchLds<false>, vis) % 16 == 0 && offsetof(PatchLds<true>, vis) % 16 == 0,
+              "the keys are cleared with 16-byte stores");
 
 int patch_max_pixels(bool global) { return global ? kPGPixels : kPPixels; }
 bool patch_fits_global(int n_obj, int64_t n_tris) { return n_obj <= kPGOMax && n_tris < 65536; }
