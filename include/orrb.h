@@ -182,8 +182,8 @@ typedef struct {
     orrb_tuning tuning;
     int64_t render_kernels;      /* kernel launches one orrb_render_batch makes (current tuning,
                                     shadow frames included): a captured graph's kernel nodes (a call
-                                    with a stats or track destination that renders patches makes one
-                                    more per set of patches) */
+                                    with a stats or track destination makes one more per launch of
+                                    patches) */
 } orrb_layout_info;
 
 /* Validate `desc` against the context's meshes and build a layout (device tables are

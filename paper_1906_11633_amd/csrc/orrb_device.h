@@ -186,6 +186,7 @@ bool frame_fits(int64_t n_verts, int n_obj, int64_t n_tris);       // scenes hel
 bool frame_fits_global(int64_t n_verts, int n_obj, int64_t n_tris);  // in the frame kernel's scratch
 int frame_max_side();                                                // frames up to this wide and high
 void frame_limits(int *bin_max, int *surv_max);
+int patch_launches(int64_t n_patches);                   // launches that many patches take
 int patch_max_pixels(bool global);                       // largest patch (global: scenes not held in LDS)
 bool patch_fits_global(int n_obj, int64_t n_tris);       // such a scene can be rendered as patches
 size_t raster_lds_bytes(int tile_w, int tile_h, int bin_cap);

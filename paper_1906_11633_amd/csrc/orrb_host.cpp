@@ -494,16 +494,16 @@ static void schedule_patches(orrb_layout *L, const std::vector<int32_t> &patched
 }
 
 // Kernel launches of one render call: the shadow frames' (camera gather + their own),
-// vertex for the tiled path and larger scenes' patches, raster for the tiled path, the frame kernel (after a counter clear when its
-// frames are claimed at run time), the patch kernel (with counters or Tracker records a call
-// launches one more before it).
+// vertex for the tiled path and larger scenes' patches, raster for the tiled path, the frame
+// kernel (after a counter clear when its frames are claimed at run time), the patch kernel
+// (with counters or Tracker records each of its launches has one more before them).
 static int64_t render_kernels(const orrb_layout *L) {
     if (L->n_frames == 0) return 0;
     int64_t n = L->shadow ? 1 + render_kernels(L->shadow) : 0;
     if (!L->vitems.empty() || !L->titems.empty()) n += 1;
     if (!L->titems.empty()) n += 1;
     if (!L->fitems.empty()) n += 1 + L->f_dynamic;
-    n += !L->pitems.empty();
+    n += patch_launches((int64_t)L->pitems.size());
     return n;
 }
 
@@ -1108,7 +1108,7 @@ orrb_status orrb_layout_create(orrb_context *ctx, const orrb_layout_desc *d, orr
     L->all_vertex_instances = vi;
     L->all_object_instances = oi;
     build_items(L);
-    if ((int64_t)L->titems.size() > 0x7fffffff || (int64_t)L->vitems.size() > 0x7fffffff) {
+    if (std::max({L->titems.size(), L->vitems.size(), L->pitems.size()}) > 0x7fffffff) {
         delete L;
         return fail(ORRB_ERR_UNSUPPORTED, "too many tiles");
     }

@@ -620,12 +620,11 @@ __global__ __launch_bounds__(kWave) void k_patch_prepare(RenderArgs a) {
                K[0], K[1], K[2], K[3]);
 }
 
-// a.pitems: the patches of scenes held in LDS (kind 0), of larger ones, whose vertices
-// k_vertex has written (1; it also starts their Tracker records), or of both (2).
-hipError_t launch_patch(const RenderArgs &a, int kind, hipStream_t stream) {
-    if (a.n_pitems <= 0) return hipSuccess;
-    if (a.p_account || (a.out_track && kind != 1))
-        hipLaunchKernelGGL(k_patch_prepare, dim3(a.n_pitems), dim3(kWave), 0, stream, a);
+// A launch holds fewer than 2^32 threads (beyond, the grid is cut short without an error).
+constexpr int kPLaunch = 1 << 21;  // most patches of one launch
+int patch_launches(int64_t n_patches) { return (int)((n_patches + kPLaunch - 1) / kPLaunch); }
+
+static hipError_t launch_patches(const RenderArgs &a, int kind, hipStream_t stream) {
     const bool aux = a.out_alpha || a.out_track || a.out_rgb8;
     const dim3 g(a.n_pitems), b(kPT);
 #define ORRB_PATCH_KIND(KIND_, SHADE_)                                                               \
@@ -649,6 +648,22 @@ hipError_t launch_patch(const RenderArgs &a, int kind, hipStream_t stream) {
 #undef ORRB_PATCH
 #undef ORRB_PATCH_KIND
     return hipGetLastError();
+}
+
+// a.pitems: the patches of scenes held in LDS (kind 0), of larger ones, whose vertices
+// k_vertex has written (1; it also starts their Tracker records), or of both (2).
+hipError_t launch_patch(const RenderArgs &a, int kind, hipStream_t stream) {
+    const bool prepare = a.p_account || (a.out_track && kind != 1);
+    RenderArgs part = a;
+    for (int patches = prepare ? 0 : 1; patches < 2; ++patches)  // every frame is prepared before its first patch
+        for (int64_t k = 0; k < a.n_pitems; k += kPLaunch) {
+            part.pitems = a.pitems + k;
+            part.n_pitems = (int32_t)(a.n_pitems - k < kPLaunch ? a.n_pitems - k : kPLaunch);
+            if (!patches) hipLaunchKernelGGL(k_patch_prepare, dim3(part.n_pitems), dim3(kWave), 0, stream, part);
+            const hipError_t e = patches ? launch_patches(part, kind, stream) : hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+    return hipSuccess;
 }
 
 }  // namespace orrb
