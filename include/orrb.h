@@ -182,8 +182,8 @@ typedef struct {
     orrb_tuning tuning;
     int64_t render_kernels;      /* kernel launches one orrb_render_batch makes (current tuning,
                                     shadow frames included): a captured graph's kernel nodes (a call
-                                    with a stats or track destination makes one more per launch of
-                                    patches) */
+                                    with a stats or track destination may make one more per launch
+                                    of patches) */
 } orrb_layout_info;
 
 /* Validate `desc` against the context's meshes and build a layout (device tables are
@@ -390,9 +390,9 @@ orrb_status orrb_validate_batch(orrb_context *ctx, const orrb_layout *layout, co
  * by the caller; consecutive calls on one stream are safe.  Errors: as
  * orrb_render_batch, plus ORRB_ERR_UNSUPPORTED (with nothing enqueued) when the
  * batch needs more workspace than the array holds (orrb_layout_info.workspace_bytes
- * > ORRB_NOALLOC_SCRATCH_BYTES; the frame path needs a few hundred bytes, 8 bytes per
- * frame more when it renders patches, the tiled path 16 bytes per vertex instance plus
- * 64 per object instance). */
+ * > ORRB_NOALLOC_SCRATCH_BYTES; the frame path needs a few hundred bytes, the tiled path
+ * 16 bytes per vertex instance plus 64 per object instance; counter sums of patches, 8
+ * bytes per frame cut into several, do not count). */
 #define ORRB_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)
 orrb_status orrb_render_batch_noalloc(orrb_context *ctx, const orrb_layout *layout, const orrb_scenes *scenes,
                                       const orrb_cameras *cameras, const orrb_params *params,

@@ -28,7 +28,7 @@ struct FrameInfo {
     int32_t light_begin, n_lights;
     int32_t track_base;         // first tracker record (frame, object) of the frame
     int32_t mode;               // scene data: 0 in LDS, 1 in the global frame scratch, 2 k_vertex's records (patches)
-    int32_t pad0;
+    int32_t account;            // patches: slot of their counter sums, kOnePatch or kUncounted
 };
 
 // Per object, built on the host from the layout and the mesh pool.
@@ -39,6 +39,10 @@ struct ObjInfo {
     int32_t scene_tbase;           // scene-local triangle ID of its first triangle
     int32_t mesh;                  // its mesh (bounding box in mesh_box)
 };
+
+// FrameInfo::account where a frame's patches need no sums: its only patch counts by itself, or
+// the frame kernel's limits do not apply.
+constexpr int32_t kOnePatch = -1, kUncounted = -2;
 
 // Work item of k_patch: the pixels [x0, x1) x [y0, y1) of a frame (at most
 // patch_max_pixels of them); parts: the frame's patches.
@@ -62,9 +66,10 @@ struct RenderArgs {
     const int32_t *fitems;  // frames rendered by k_frame
     const PatchItem *pitems;  // rectangles of frames rendered by k_patch
     int32_t n_pitems;
-    int32_t p_side;            // the frame kernel's largest frame
     PatchLimits p_limits[2];   // of scenes held in LDS and of larger ones
-    unsigned long long *p_account;   // per frame: sums of its patches (patch_account), or null
+    unsigned long long *p_account;   // sums of the frames cut into several patches (patch_account), or
+                                     // null: the call counts no limits
+    int32_t n_account;
     const int32_t *light_type;
     int32_t n_vitems, n_titems, n_fitems;
     int32_t v_wave;         // k_vertex: a wave per item (1) or a workgroup (0)
@@ -196,7 +201,9 @@ orrb_status debug_validate(orrb_context *ctx, const orrb_layout *L, const orrb_s
 orrb_status render_impl(orrb_context *ctx, const orrb_layout *L, const orrb_scenes *sc, const orrb_cameras *cam,
                         const orrb_params *par, const orrb_outputs *out, void *workspace, size_t workspace_bytes,
                         void *stream, bool timing);
-size_t render_workspace_bytes(const orrb_layout *L);  // workspace of one render call (current tuning)
+size_t render_workspace_bytes(const orrb_layout *L);
+size_t patch_sum_bytes(const orrb_layout *L);  // of these, the patches' counter sums
+size_t patch_sum_bytes(const orrb_layout *L);  // of these, for patches' counter sums  // workspace of one render call (current tuning)
 hipError_t scratch_init(int device);  // resolve the device's copy of the fixed scratch (orrb_noalloc.cpp)
 
 }  // namespace orrb

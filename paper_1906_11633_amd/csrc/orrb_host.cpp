@@ -200,6 +200,7 @@ struct orrb_layout {
     std::vector<PatchItem> pitems;  // patches of LDS-held and of larger scenes (see schedule_patches)
     int64_t gp_items = 0;           // of these, of larger scenes
     int64_t p_frames = 0, gp_frames = 0;     // frames rendered as such patches
+    int64_t account_slots = 0;               // of these, frames whose patches sum up counters
     int64_t f_frames = 0;          // frames on the frame kernel
     int32_t f_grid = 0;            // its persistent grid
     int32_t f_dynamic = 0;         // 1: frames claimed from a counter (uneven batch)
@@ -269,7 +270,7 @@ static FrameScratch frame_scratch(int64_t gframes, int64_t frame_kernel_frames, 
 }
 
 static WsLayout ws_layout(int64_t vertex_instances, int64_t object_instances, const FrameScratch &fs = FrameScratch(),
-                          int64_t patched_frames = 0) {
+                          int64_t account_slots = 0) {
     WsLayout w;
     size_t off = 0;
     w.vtx_pos = off;
@@ -280,8 +281,8 @@ static WsLayout ws_layout(int64_t vertex_instances, int64_t object_instances, co
     off = al256(off + sizeof(int4) * (size_t)object_instances);
     w.queue = off;
     off = al256(off + 64);
-    w.account = off;  // 8 bytes per frame when some are rendered as patches
-    off = al256(off + sizeof(uint64_t) * (size_t)patched_frames);
+    w.account = off;
+    off = al256(off + sizeof(uint64_t) * (size_t)account_slots);
     w.fscratch = off;
     w.fs_stride = fs.stride;
     w.fs_verts = fs.verts;
@@ -372,7 +373,7 @@ static void patch_grid(int W, int H, int cap, double share, bool heavy, bool nar
     constexpr int U = 4;
     const int nx = (W + U - 1) / U, side = frame_max_side();
     const bool large = W > side || H > side, some = !large && heavy && narrow && share >= 1.7;
-    auto fits = [&](int x, int y) { return (int64_t)U * ((nx + x - 1) / x) * ((H + y - 1) / y) <= cap; };
+    auto fits = [&](int x, int y) { return (int64_t)std::min(W, U * ((nx + x - 1) / x)) * ((H + y - 1) / y) <= cap; };
     int x = 1, y = 1;
     for (y = 1; y <= H; ++y) {  // the least number of columns, in more rows where they get too narrow
         for (x = 1; x < nx && !fits(x, y); ++x) {
@@ -491,6 +492,16 @@ static void schedule_patches(orrb_layout *L, const std::vector<int32_t> &patched
     std::vector<PatchItem> sorted(items.size());
     for (size_t k = 0; k < order.size(); ++k) sorted[k] = items[order[k]];
     items.swap(sorted);
+    // Counter sums, for frames that the frame kernel could take, where several patches share
+    // one (with more frames than CUs only those of a last round: at most as many as CUs).
+    L->account_slots = 0;
+    const int side = frame_max_side();
+    for (const PatchItem &it : items) {
+        FrameInfo &fi = L->frames[it.frame];
+        if ((it.x0 | it.y0) != 0 || fi.n_obj == 0 || fi.width > side || fi.height > side) continue;
+        if (fi.mode == 2 && L->tuning.path != 2) continue;
+        fi.account = it.parts > 1 ? (int32_t)L->account_slots++ : kOnePatch;
+    }
 }
 
 // Kernel launches of one render call: the shadow frames' (camera gather + their own),
@@ -511,7 +522,7 @@ static WsLayout ws_layout(const orrb_layout *L) {
     const FrameScratch fs =
         frame_scratch(L->gframes, L->f_frames, L->gf_verts, L->gf_tris, L->tuning.bin_cap,
                       L->ctx ? L->ctx->n_cu : 256);
-    return ws_layout(L->tiled_vertex_instances, L->tiled_object_instances, fs, L->p_frames + L->gp_frames ? L->n_frames : 0);
+    return ws_layout(L->tiled_vertex_instances, L->tiled_object_instances, fs, L->account_slots);
 }
 
 // Workspace enough for every valid tuning: every frame on the tiled path, plus the
@@ -591,6 +602,7 @@ static void build_items(orrb_layout *L) {
         FrameInfo &fi = L->frames[f];
         fi.tiles_x = (fi.width + TW - 1) / TW;
         fi.mode = 0;
+        fi.account = kUncounted;
         fi.vbase = 0;
         fi.oi_base = 0;
         if (path != 1 && L->fits[f] == 1) {
@@ -1091,7 +1103,7 @@ orrb_status orrb_layout_create(orrb_context *ctx, const orrb_layout_desc *d, orr
                      : patch_fits_global(fi.n_obj, L->scene_tris[s])                           ? 3
                                                                                                : 0;
         fi.mode = 0;
-        fi.pad0 = 0;
+        fi.account = kUncounted;
         pix += (int64_t)fi.width * fi.height;
         L->max_frame_pixels = std::max<int64_t>(L->max_frame_pixels, (int64_t)fi.width * fi.height);
         vi += L->scene_verts[s];
@@ -1219,6 +1231,10 @@ orrb_status orrb_layout_set_tuning(orrb_layout *L, const orrb_tuning *t) {
 
 size_t orrb::render_workspace_bytes(const orrb_layout *L) { return call_ws(L).total; }
 
+size_t orrb::patch_sum_bytes(const orrb_layout *L) {
+    return al256(sizeof(uint64_t) * (size_t)L->account_slots) + (L->shadow ? patch_sum_bytes(L->shadow) : 0);
+}
+
 // A render call: host checks, then the kernels on `stream`.  With `timing` false it
 // records no kernel-timing events (and so creates none).
 orrb_status orrb::render_impl(orrb_context *ctx, const orrb_layout *L, const orrb_scenes *sc, const orrb_cameras *cam,
@@ -1339,7 +1355,7 @@ orrb_status orrb::render_impl(orrb_context *ctx, const orrb_layout *L, const orr
         if (k == 2 && e == hipSuccess) {
             a.pitems = L->tab.at<PatchItem>(L->o_pitems);
             a.n_pitems = (int32_t)L->pitems.size();
-            a.p_side = frame_max_side();
+            a.n_account = (int32_t)L->account_slots;
             frame_limits(&a.p_limits[0].bin_max, &a.p_limits[0].surv_max);
             if (L->tuning.path == 2) {  // the frame kernel's global scratch would have had these limits
                 const FrameScratch fs = frame_scratch(1, 1, 1, L->gp_tris, L->tuning.bin_cap, 1);

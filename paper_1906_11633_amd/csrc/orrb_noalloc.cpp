@@ -16,8 +16,11 @@
 
 namespace {
 
-constexpr size_t kScratchBytes = size_t(64) << 20;  // ORRB_NOALLOC_SCRATCH_BYTES
-static_assert(kScratchBytes == ORRB_NOALLOC_SCRATCH_BYTES, "header and library disagree on the scratch size");
+// Room for the patches' counter sums comes on top, so that rendering frames as patches makes no
+// batch too large: 8 bytes per frame of a last round (at most as many as CUs), once for the
+// frames and once for their shadow frames.
+constexpr size_t kSumBytes = 16 << 10;
+constexpr size_t kScratchBytes = ORRB_NOALLOC_SCRATCH_BYTES + kSumBytes;
 
 // One copy per device, alive until the process ends.  Every call on a device shares it.
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -57,12 +60,12 @@ extern "C" orrb_status orrb_render_batch_noalloc(orrb_context *ctx, const orrb_l
     orrb::set_error(ORRB_OK, "");  // the thread's last error describes this call only
     if (!ctx || !layout) return orrb::set_error(ORRB_ERR_INVALID_ARGUMENT, "NULL handle");
     const size_t need = orrb::render_workspace_bytes(layout);
-    if (need > kScratchBytes) {
+    if (need > kScratchBytes || need - orrb::patch_sum_bytes(layout) > ORRB_NOALLOC_SCRATCH_BYTES) {
         char msg[192];
         snprintf(msg, sizeof(msg),
                  "the batch needs %zu bytes of workspace; orrb_render_batch_noalloc holds at most %zu "
                  "(use orrb_render_batch with a caller workspace)",
-                 need, kScratchBytes);
+                 need, ORRB_NOALLOC_SCRATCH_BYTES);
         return orrb::set_error(ORRB_ERR_UNSUPPORTED, msg);
     }
     void *ws = scratch_address(orrb::context_device(ctx));

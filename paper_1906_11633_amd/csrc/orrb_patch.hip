@@ -236,13 +236,16 @@ ORRB_INLINE int patch_setup(int4 A, int4 B, int4 C, int px0, int py0, int pw, in
 
 // The bin-overflow and survivor counters describe frames as the frame kernel renders them
 // whole.  A patch adds the triangles whose first pixel it holds (so each counts once) and
-// their 64 x 4 tiles to its frame's sums; the frame's last patch compares them with the
-// frame kernel's limits.
-ORRB_INLINE void patch_account(const RenderArgs &a, const PatchItem &it, unsigned entries, unsigned survivors,
+// their 64 x 4 tiles to its frame's sums; the frame's last patch (or only one, which needs no
+// sums) compares them with the frame kernel's limits.
+ORRB_INLINE void patch_account(const RenderArgs &a, const PatchItem &it, int slot, unsigned entries, unsigned survivors,
                                const PatchLimits &limits) {
-    const unsigned long long add = (1ull << 52) | ((unsigned long long)survivors << 32) | entries;
-    const unsigned long long sum = atomicAdd(a.p_account + it.frame, add) + add;
-    if ((int)(sum >> 52) != it.parts) return;
+    unsigned long long sum = ((unsigned long long)survivors << 32) | entries;
+    if (slot >= 0) {
+        sum += 1ull << 52;
+        sum += atomicAdd(a.p_account + slot, sum);
+        if ((int)(sum >> 52) != it.parts) return;
+    }
     const bool overflow = (unsigned)sum > (unsigned)limits.bin_max;
     stat_add(a, ORRB_STAT_BIN_OVERFLOW, overflow ? 1u : 0u);
     stat_add(a, ORRB_STAT_SURVIVOR_RESETUP, !overflow && ((sum >> 32) & 0xfffff) > (unsigned)limits.surv_max ? 1u : 0u);
@@ -251,11 +254,11 @@ ORRB_INLINE void patch_account(const RenderArgs &a, const PatchItem &it, unsigne
 template <bool AUX, bool G, int SHADE>
 ORRB_INLINE void patch_render(const RenderArgs &a, PatchLds<G> &S, const PatchItem it) {
     const PatchLimits limits = a.p_limits[G];
-    const bool account = a.p_account && limits.bin_max > 0;
     const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid) / kWave;
     const int f = it.frame;
     const FrameInfo fi = a.frames[f];
     const int n_obj = fi.n_obj;
+    const bool account = a.p_account && limits.bin_max > 0 && fi.account != kUncounted;
     const int px0 = it.x0, py0 = it.y0, pw = it.x1 - it.x0, ph = it.y1 - it.y0, n_pix = pw * ph;
 
     // ---- 1: objects, lights, tables ----
@@ -428,7 +431,7 @@ ORRB_INLINE void patch_render(const RenderArgs &a, PatchLds<G> &S, const PatchIt
             const int n = t >= 0 ? patch_setup(verts.get(base + tri.x), verts.get(base + tri.z), verts.get(base + tri.y),
                                                px0, py0, pw, ph, T)
                                  : 0;
-            if (account && n > 0 && fi.width <= a.p_side && fi.height <= a.p_side) {
+            if (account && n > 0) {
                 const int xmin = min(T.xa, min(T.xb, T.xc)), xmax = max(T.xa, max(T.xb, T.xc));
                 const int ymin = min(T.ya, min(T.yb, T.yc)), ymax = max(T.ya, max(T.yb, T.yc));
                 const int i0 = max(ceil256(xmin - 128), 0), j0 = max(ceil256(ymin - 128), 0);
@@ -476,7 +479,7 @@ ORRB_INLINE void patch_render(const RenderArgs &a, PatchLds<G> &S, const PatchIt
         if (survivors) atomicAdd(&S.account[1], survivors);
     }
     __syncthreads();
-    if (account && tid == 0) patch_account(a, it, S.account[0], S.account[1], limits);
+    if (account && tid == 0) patch_account(a, it, fi.account, S.account[0], S.account[1], limits);
 
     // ---- 4: shade and store ----
     const CamF cam = frame_camera(a, f);
@@ -611,7 +614,7 @@ __global__ __launch_bounds__(kWave) void k_patch_prepare(RenderArgs a) {
     const PatchItem it = a.pitems[blockIdx.x];
     if ((it.x0 | it.y0) != 0) return;
     const FrameInfo fi = a.frames[it.frame];
-    if (a.p_account && threadIdx.x == 0) a.p_account[it.frame] = 0ull;
+    if (a.p_account && fi.account >= 0 && threadIdx.x == 0) a.p_account[fi.account] = 0ull;
     const int k = threadIdx.x;
     if (!a.out_track || k >= fi.n_obj || fi.n_obj > kPOMax) return;  // (larger scenes: k_vertex)
     const float *V = a.view + 12 * (int64_t)it.frame, *P = a.pose + 12 * (int64_t)(fi.obj_begin + k);
@@ -653,7 +656,7 @@ static hipError_t launch_patches(const RenderArgs &a, int kind, hipStream_t stre
 // a.pitems: the patches of scenes held in LDS (kind 0), of larger ones, whose vertices
 // k_vertex has written (1; it also starts their Tracker records), or of both (2).
 hipError_t launch_patch(const RenderArgs &a, int kind, hipStream_t stream) {
-    const bool prepare = a.p_account || (a.out_track && kind != 1);
+    const bool prepare = (a.p_account && a.n_account > 0) || (a.out_track && kind != 1);
     RenderArgs part = a;
     for (int patches = prepare ? 0 : 1; patches < 2; ++patches)  // every frame is prepared before its first patch
         for (int64_t k = 0; k < a.n_pitems; k += kPLaunch) {
