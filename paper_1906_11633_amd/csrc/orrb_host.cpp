@@ -571,15 +571,30 @@ static CallWs call_ws(const orrb_layout *L) { return call_ws(L, L->shadow ? ws_l
 // vertex kernel) but spread over the chip.  Measured (one MI355X, us, frame kernel / patches):
 // 24 uneven frames 175 / 47, 192: 365 / 146, 384: 382 / 256, 768 (work over the CUs 0.96 of
 // the costliest frame): 509 / 514 to 541, 1,536: 713 / 890, 3,072: 1,399 / 1,694.
+// Patches also need the vertex records of every frame, the frame kernel one scratch slice a
+// workgroup: frames whose records take more than the slices (scenes of many vertices and few
+// triangles in a batch of more frames than CUs) stay on the frame kernel, so that path 2 never
+// needs more workspace than the slices of the smallest bin capacity.
 static bool frame_scratch_pays(const orrb_layout *L) {
+    const int n_cu = L->ctx ? L->ctx->n_cu : 256;
     double sum = 0.0, most = 0.0;
+    int64_t n = 0, n_large = 0, verts = 0, objs = 0, max_verts = 0, max_tris = 0;
     for (int32_t f = 0; f < (int32_t)L->n_frames; ++f) {
         if (L->fits[f] != 1 && L->fits[f] != 2) continue;
         const double c = frame_cost(L, f, L->fits[f] == 2);
         sum += c;
         most = std::max(most, c);
+        ++n;
+        if (L->fits[f] != 2) continue;
+        const FrameInfo &fi = L->frames[f];
+        ++n_large;
+        objs += fi.n_obj;
+        verts += L->scene_verts[fi.scene];
+        max_verts = std::max(max_verts, L->scene_verts[fi.scene]);
+        max_tris = std::max(max_tris, L->scene_tris[fi.scene]);
     }
-    return sum >= 0.9 * (L->ctx ? L->ctx->n_cu : 256) * most;
+    const FrameScratch fs = frame_scratch(n_large, n, max_verts, max_tris, 256, n_cu);
+    return sum >= 0.9 * n_cu * most || ws_layout(verts, objs, FrameScratch(), n).total > ws_layout(0, 0, fs).total;
 }
 
 // Split frames between the frame kernel, patches and the tiled path and build the work

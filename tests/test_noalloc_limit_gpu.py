@@ -37,7 +37,13 @@ def _largest_mesh_beside_patches():
     return _two_scenes(_padded(S.box_mesh(1), n), S.box_mesh(2), [(64, 64)] + [(128, 128)] * 40)
 
 
-@pytest.mark.parametrize("make,path", [(_largest_mesh_beside_patches, 0)])
+def _more_vertex_records_than_scratch():
+    # 112 kB of vertex records a frame, 2 triangles in all frames but one
+    return _two_scenes(_padded(S.plane_mesh(80, 80, 1.5, 1.5), 7000), _padded(S.plane_mesh(1, 1, 1.5, 1.5), 7000),
+                       [(200, 200)] + [(16, 16)] * 1000)
+
+
+@pytest.mark.parametrize("make,path", [(_largest_mesh_beside_patches, 0), (_more_vertex_records_than_scratch, 2)])
 def test_batches_that_fit_stay_accepted(renderer, make, path):  # noqa: F811
     import torch
     from paper_1906_11633_amd.renderer import render_batch_noalloc
