@@ -194,7 +194,7 @@ struct orrb_layout {
     std::vector<uint8_t> fits;
     // frames on the frame kernel with scene data in global scratch (tuning path 2)
     int64_t gframes = 0, gf_verts = 0, gf_tris = 0;
-    int64_t gp_tris = 0;  // most triangles of a larger scene rendered as patches
+    int64_t gp_tris = 0;  // most triangles of a scratch-sized scene rendered as patches
     std::vector<int2> vitems, titems;
     std::vector<int32_t> fitems;  // frame-kernel schedule (see schedule_frames)
     std::vector<PatchItem> pitems;  // patches of LDS-held and of larger scenes (see schedule_patches)
@@ -499,7 +499,7 @@ static void schedule_patches(orrb_layout *L, const std::vector<int32_t> &patched
     for (const PatchItem &it : items) {
         FrameInfo &fi = L->frames[it.frame];
         if ((it.x0 | it.y0) != 0 || fi.n_obj == 0 || fi.width > side || fi.height > side) continue;
-        if (fi.mode == 2 && L->tuning.path != 2) continue;
+        if (fi.mode == 2 && (L->tuning.path != 2 || L->fits[it.frame] != 2)) continue;
         fi.account = it.parts > 1 ? (int32_t)L->account_slots++ : kOnePatch;
     }
 }
@@ -640,7 +640,7 @@ static void build_items(orrb_layout *L) {
         if (path != 1 && L->fits[f] != 0) {
             gpatched.push_back((int32_t)f);
             fi.mode = 2;
-            L->gp_tris = std::max<int64_t>(L->gp_tris, L->scene_tris[fi.scene]);
+            if (L->fits[f] == 2) L->gp_tris = std::max<int64_t>(L->gp_tris, L->scene_tris[fi.scene]);
             continue;
         }
         const int ty = (fi.height + TH - 1) / TH;
