@@ -201,9 +201,13 @@ orrb_status debug_validate(orrb_context *ctx, const orrb_layout *L, const orrb_s
 orrb_status render_impl(orrb_context *ctx, const orrb_layout *L, const orrb_scenes *sc, const orrb_cameras *cam,
                         const orrb_params *par, const orrb_outputs *out, void *workspace, size_t workspace_bytes,
                         void *stream, bool timing);
-size_t render_workspace_bytes(const orrb_layout *L);
-size_t patch_sum_bytes(const orrb_layout *L);  // of these, the patches' counter sums
-size_t patch_sum_bytes(const orrb_layout *L);  // of these, for patches' counter sums  // workspace of one render call (current tuning)
+size_t render_workspace_bytes(const orrb_layout *L);  // workspace of one render call (current tuning)
+size_t patch_sum_bytes(const orrb_layout *L);         // of these, the patches' counter sums
+// What renders the layout's frames, shadow frames included, with the current tuning.
+struct PathUse {
+    bool tiled, other, scratch;  // the tiled path; frame kernel or patches; the frame kernel's scratch
+};
+PathUse layout_use(const orrb_layout *L);
 hipError_t scratch_init(int device);  // resolve the device's copy of the fixed scratch (orrb_noalloc.cpp)
 
 }  // namespace orrb

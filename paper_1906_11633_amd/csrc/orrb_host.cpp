@@ -1246,6 +1246,15 @@ orrb_status orrb_layout_set_tuning(orrb_layout *L, const orrb_tuning *t) {
 
 size_t orrb::render_workspace_bytes(const orrb_layout *L) { return call_ws(L).total; }
 
+PathUse orrb::layout_use(const orrb_layout *L) {
+    PathUse u{!L->titems.empty(), !L->fitems.empty() || !L->pitems.empty(), L->gframes > 0};
+    if (L->shadow) {
+        const PathUse s = layout_use(L->shadow);
+        u = {u.tiled || s.tiled, u.other || s.other, u.scratch || s.scratch};
+    }
+    return u;
+}
+
 size_t orrb::patch_sum_bytes(const orrb_layout *L) {
     return al256(sizeof(uint64_t) * (size_t)L->account_slots) + (L->shadow ? patch_sum_bytes(L->shadow) : 0);
 }
