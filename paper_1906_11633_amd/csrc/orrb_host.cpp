@@ -57,13 +57,12 @@ struct DevBuf {
     ~DevBuf() {
         if (p) (void)hipFree(p);
     }
-    // spare: allocate at least that much (a pool that grows mesh by mesh)
-    hipError_t upload(const void *src, size_t n, size_t spare = 0) {
+    // grow: allocate ahead (a pool that grows mesh by mesh), twice what there was but at most 16 MB more
+    hipError_t upload(const void *src, size_t n, bool grow = false) {
         if (n > bytes) {
+            const size_t ahead = bytes + std::min(bytes, size_t(16) << 20), want = grow ? std::max(n, ahead) : n;
             if (p) (void)hipFree(p);
             p = nullptr;
-            bytes = 0;
-            const size_t want = n > spare ? n : spare;
             bytes = want;
             hipError_t e = hipMalloc(&p, want);
             if (e != hipSuccess && want > n) {
@@ -943,11 +942,11 @@ orrb_status orrb_add_mesh(orrb_context *ctx, const float *pos, const float *nrm,
         ctx->mesh_box[b0 + 3 + k % 3] = std::max(ctx->mesh_box[b0 + 3 + k % 3], pos[k]);
     }
     ScopedDevice sd(ctx->device);
-    hipError_t e = ctx->d_pos.upload(ctx->pos.data(), sizeof(float4) * ctx->pos.size(), 2 * ctx->d_pos.bytes);
-    if (e == hipSuccess) e = ctx->d_nrm.upload(ctx->nrm.data(), sizeof(float4) * ctx->nrm.size(), 2 * ctx->d_nrm.bytes);
-    if (e == hipSuccess) e = ctx->d_tri.upload(ctx->tri.data(), sizeof(int4) * ctx->tri.size(), 2 * ctx->d_tri.bytes);
-    if (e == hipSuccess) e = ctx->d_uv.upload(ctx->uv.data(), sizeof(float2) * ctx->uv.size(), 2 * ctx->d_uv.bytes);
-    if (e == hipSuccess) e = ctx->d_box.upload(ctx->mesh_box.data(), sizeof(float) * ctx->mesh_box.size(), 2 * ctx->d_box.bytes);
+    hipError_t e = ctx->d_pos.upload(ctx->pos.data(), sizeof(float4) * ctx->pos.size(), true);
+    if (e == hipSuccess) e = ctx->d_nrm.upload(ctx->nrm.data(), sizeof(float4) * ctx->nrm.size(), true);
+    if (e == hipSuccess) e = ctx->d_tri.upload(ctx->tri.data(), sizeof(int4) * ctx->tri.size(), true);
+    if (e == hipSuccess) e = ctx->d_uv.upload(ctx->uv.data(), sizeof(float2) * ctx->uv.size(), true);
+    if (e == hipSuccess) e = ctx->d_box.upload(ctx->mesh_box.data(), sizeof(float) * ctx->mesh_box.size(), true);
     if (e != hipSuccess) {
         ctx->mesh_box.resize(b0);
         ctx->pos.resize(v0);
