@@ -57,10 +57,14 @@ struct DevBuf {
     ~DevBuf() {
         if (p) (void)hipFree(p);
     }
-    // grow: allocate ahead (a pool that grows mesh by mesh), twice what there was but at most 16 MB more
-    hipError_t upload(const void *src, size_t n, bool grow = false) {
+    hipError_t upload(const void *src, size_t n) { return append(src, 0, n); }
+    // src's first `have` bytes are there already and keep their place while there is room: renders
+    // in flight may be reading them.  have > 0 allocates ahead (a pool that grows mesh by mesh),
+    // twice what there was but at most 16 MB more.
+    hipError_t append(const void *src, size_t have, size_t n) {
         if (n > bytes) {
-            const size_t ahead = bytes + std::min(bytes, size_t(16) << 20), want = grow ? std::max(n, ahead) : n;
+            const size_t ahead = bytes + std::min(bytes, size_t(16) << 20), want = have ? std::max(n, ahead) : n;
+            have = 0;
             if (p) (void)hipFree(p);
             p = nullptr;
             bytes = want;
@@ -76,8 +80,8 @@ struct DevBuf {
                 return e;
             }
         }
-        if (n == 0) return hipSuccess;
-        return hipMemcpy(p, src, n, hipMemcpyHostToDevice);
+        if (n == have) return hipSuccess;
+        return hipMemcpy((char *)p + have, (const char *)src + have, n - have, hipMemcpyHostToDevice);
     }
 };
 
@@ -942,11 +946,11 @@ orrb_status orrb_add_mesh(orrb_context *ctx, const float *pos, const float *nrm,
         ctx->mesh_box[b0 + 3 + k % 3] = std::max(ctx->mesh_box[b0 + 3 + k % 3], pos[k]);
     }
     ScopedDevice sd(ctx->device);
-    hipError_t e = ctx->d_pos.upload(ctx->pos.data(), sizeof(float4) * ctx->pos.size(), true);
-    if (e == hipSuccess) e = ctx->d_nrm.upload(ctx->nrm.data(), sizeof(float4) * ctx->nrm.size(), true);
-    if (e == hipSuccess) e = ctx->d_tri.upload(ctx->tri.data(), sizeof(int4) * ctx->tri.size(), true);
-    if (e == hipSuccess) e = ctx->d_uv.upload(ctx->uv.data(), sizeof(float2) * ctx->uv.size(), true);
-    if (e == hipSuccess) e = ctx->d_box.upload(ctx->mesh_box.data(), sizeof(float) * ctx->mesh_box.size(), true);
+    hipError_t e = ctx->d_pos.append(ctx->pos.data(), sizeof(float4) * v0, sizeof(float4) * ctx->pos.size());
+    if (e == hipSuccess) e = ctx->d_nrm.append(ctx->nrm.data(), sizeof(float4) * v0, sizeof(float4) * ctx->nrm.size());
+    if (e == hipSuccess) e = ctx->d_tri.append(ctx->tri.data(), sizeof(int4) * t0, sizeof(int4) * ctx->tri.size());
+    if (e == hipSuccess) e = ctx->d_uv.append(ctx->uv.data(), sizeof(float2) * v0, sizeof(float2) * ctx->uv.size());
+    if (e == hipSuccess) e = ctx->d_box.append(ctx->mesh_box.data(), sizeof(float) * b0, sizeof(float) * ctx->mesh_box.size());
     if (e != hipSuccess) {
         ctx->mesh_box.resize(b0);
         ctx->pos.resize(v0);
