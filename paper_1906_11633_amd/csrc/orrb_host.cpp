@@ -182,6 +182,16 @@ struct orrb_context {
     bool debug_validate = false;  // every render call first checks its preconditions
 };
 
+// Who renders the frames that are not on the tiled path.
+struct FramePlan {
+    std::vector<int32_t> fitems;    // frame-kernel schedule (see schedule_frames)
+    int32_t f_grid = 0;             // its persistent grid
+    int32_t f_dynamic = 0;          // 1: frames claimed from a counter (uneven batch)
+    std::vector<PatchItem> pitems;  // patches (see schedule_patches)
+    int64_t p_frames = 0;           // frames of LDS-held scenes rendered as patches
+    size_t o_fitems = 0, o_pitems = 0;
+};
+
 struct orrb_layout {
     orrb_context *ctx = nullptr;
     int64_t n_scenes = 0, n_objects = 0, n_lights = 0, n_frames = 0;
@@ -201,18 +211,13 @@ struct orrb_layout {
     int64_t gframes = 0, gf_verts = 0, gf_tris = 0;
     int64_t gp_tris = 0;  // most triangles of a scratch-sized scene rendered as patches
     std::vector<int2> vitems, titems;
-    std::vector<int32_t> fitems;  // frame-kernel schedule (see schedule_frames)
-    std::vector<PatchItem> pitems;  // patches of LDS-held and of larger scenes (see schedule_patches)
-    int64_t gp_items = 0;           // of these, of larger scenes
-    int64_t p_frames = 0, gp_frames = 0;     // frames rendered as such patches
-    int64_t account_slots = 0;               // of these, frames whose patches sum up counters
-    int64_t f_frames = 0;          // frames on the frame kernel
-    int32_t f_grid = 0;            // its persistent grid
-    int32_t f_dynamic = 0;         // 1: frames claimed from a counter (uneven batch)
+    FramePlan plan[2];               // [1]: for calls that write at most lean_bytes
+    int64_t lean_bytes[2] = {0, 0};  // without and with alpha, Tracker records or 8-bit RGB (0: never)
+    int64_t gp_items = 0, gp_frames = 0;  // patches of larger scenes (in every plan) and their frames
+    int64_t account_slots = 0;            // frames whose patches sum up counters
     std::vector<int32_t> light_type;
     Packed tab;  // frames, objs, vitems, titems, fitems, pitems, light_type, spot tables
-    size_t o_pitems = 0;
-    size_t o_frames = 0, o_objs = 0, o_vitems = 0, o_titems = 0, o_fitems = 0, o_light_type = 0;
+    size_t o_frames = 0, o_objs = 0, o_vitems = 0, o_titems = 0, o_light_type = 0;
     // spot lights (type 2) with shadow maps: one N x N depth frame per spot light, from
     // its shadow camera, rendered by a sub-layout before the frames themselves
     int64_t n_spot = 0;
@@ -330,71 +335,89 @@ static int32_t vertex_by_wave(const orrb_layout *L, int64_t n) {
 // workgroup takes the next unclaimed frame from a counter as it finishes one, so the
 // workgroups end within about one light frame of each other whatever the estimate's
 // error.
-static void schedule_frames(orrb_layout *L) {
-    const int64_t n = (int64_t)L->fitems.size();
-    L->f_frames = n;
-    L->f_grid = (int32_t)std::min<int64_t>(n, L->ctx ? L->ctx->n_cu : 256);
-    L->f_dynamic = 0;
+static void schedule_frames(const orrb_layout *L, FramePlan &plan) {
+    const int64_t n = (int64_t)plan.fitems.size();
+    plan.f_grid = (int32_t)std::min<int64_t>(n, L->ctx ? L->ctx->n_cu : 256);
+    plan.f_dynamic = 0;
     if (n == 0) return;
     std::vector<double> cost(n);
     bool uniform = true;
     for (int64_t k = 0; k < n; ++k) {
-        cost[k] = frame_cost(L, L->fitems[k], L->frames[L->fitems[k]].mode != 0);
+        cost[k] = frame_cost(L, plan.fitems[k], L->frames[plan.fitems[k]].mode != 0);
         uniform = uniform && cost[k] == cost[0];
     }
-    if (uniform || n <= L->f_grid) return;
+    if (uniform || n <= plan.f_grid) return;
     std::vector<int64_t> order(n);
     for (int64_t k = 0; k < n; ++k) order[k] = k;
     std::stable_sort(order.begin(), order.end(), [&](int64_t x, int64_t y) { return cost[x] > cost[y]; });
     std::vector<int32_t> sorted(n);
-    for (int64_t k = 0; k < n; ++k) sorted[k] = L->fitems[order[k]];
-    L->fitems.swap(sorted);
-    L->f_dynamic = 1;
+    for (int64_t k = 0; k < n; ++k) sorted[k] = plan.fitems[order[k]];
+    plan.fitems.swap(sorted);
+    plan.f_dynamic = 1;
 }
 
-// Grid of columns (of whole 4-pixel units) and rows that cuts a W x H frame into patches of at
-// most `cap` pixels.  `share`: the CUs there are for it.  `heavy`: its geometry is worth
-// sharing out finely and the batch's rounds can be foreseen: 2,048 triangles and more held in
-// LDS, frames of one cost (231 mixed frames: 216 us without and 230 with the finer grids, 322:
-// 267 and 276, 131 frames of one capsule: 20.3 and 21.5).  `narrow`: columns below 28 pixels may be
-// used.  They write part of each 128-byte line, which costs bandwidth once a batch's
-// outputs no longer fit the 256 MB cache, some 8 M pixels (148 hand frames of 256 x 256: 124 us
-// in 5 x 2 cells, 135 in 10 columns; 104 frames: 108 and 92).
-//   - Many CUs: strips of the frame's width (of 256 pixels or so of a wider frame), a few more
-//     than the CUs, as the outer ones are light; frames beyond 256 x 256, whose outer patches
-//     are often empty, twice as many.  48 hand frames of 128 x 128: 33 us in 6 rows, 37 in 6
-//     columns; 12 of 200 x 200: 23 in 24 rows, 26 in 3 x 12.
-//     Small frames down to 3 rows (68 of 88 x 88: 37 us, 38 in 7 columns), others from 5 on.
-//   - Few: as few patches as the pixels allow, since each repeats geometry, and in columns,
-//     which repeat less than rows (hand scenes, 120 frames of 200 x 200, 77 us in 7 columns, 85
-//     in 7 rows), none narrower than 28 pixels.
-//   - Between (1.7 CUs and more a frame): up to 1.9 columns a CU and frame, of 18 pixels or
-//     more, so that two rounds even out (72 frames of 128 x 128: 50 us in 3 columns, 41 in 6;
-//     144 of 64 x 64: 41 us whole, 55 in 2, 39 in 3), unless two rows just fill the chip
-//     or three columns are needed anyhow and there are few CUs (120 of 128 x 128: 51 us in
-//     3 columns, 55 in 4).
-static void patch_grid(int W, int H, int cap, double share, bool heavy, bool narrow, int *cols,
-                       int *rows) {
-    constexpr int U = 4;
-    const int nx = (W + U - 1) / U, side = frame_max_side();
-    const bool large = W > side || H > side, some = !large && heavy && narrow && share >= 1.7;
+// How frames are cut into patches (patch_grid).
+struct GridRule {
+    bool heavy;    // heavy_frame
+    bool columns;  // columns allowed (else strips)
+    bool narrow;   // down to 18 pixels where that evens out two rounds (else 28): up to 8 M pixels
+                   // (148 hand frames of 256 x 256: 124 us in 5 x 2 cells, 135 in 10 columns; 104: 108, 92)
+    int unit() const { return columns ? 4 : 32; }  // cells are cut at whole units, in pixels
+};
+
+// Grid of columns (of whole units) and rows that cuts a W x H frame into patches of at most
+// `cap` pixels.  `share`: the CUs there are for it.
+//   - Strips of the frame's width (of 256 pixels or so of a wider frame): as few as the pixels
+//     allow, or as many as there are CUs where that is more (up to three no more than the CUs,
+//     as a second round of a few large patches costs as much as the first: 144 frames of 88 x
+//     88, 1.1 rounds of two strips, take 0.84 times as long whole; from four on a few more, as
+//     the outer ones are light; frames beyond 256 x 256, whose outer ones are often empty, two a
+//     CU).
+//   - With columns: they repeat less geometry than strips, but write parts of 128-byte lines, which
+//     reaches 1.9 TB/s in buffers that no cache holds (strips: 4).  Hands, us, columns /
+//     strips: 96 frames of 128 x 128 45 / 51, of 160 x 160 54 / 71, of 200 x 200 75 / 67; 128 of
+//     224 x 224 131 / 112; 128 of 200 x 200 with nothing in view 86 / 44.
+//       - Many CUs: strips all the same, a few more than the CUs.  48 hand frames of 128 x 128: 33 us
+//         in 6 rows, 37 in 6 columns; 12 of 200 x 200: 23 in 24 rows, 26 in 3 x 12.  Small frames
+//         down to 3 rows (68 of 88 x 88: 37 us, 38 in 7 columns), others from 5 on.
+//       - Few: as few patches as the pixels allow, none narrower than 28 pixels (120 frames of 200 x
+//         200: 77 us in 7 columns, 85 in 7 rows, in buffers that stay in the cache).
+//       - Between (1.7 CUs and more a frame): up to 1.9 columns a CU and frame, of 18 pixels or
+//         more, so that two rounds even out (72 frames of 128 x 128: 50 us in 3 columns, 41 in 6;
+//         144 of 64 x 64: 41 us whole, 55 in 2, 39 in 3; 140 of 40 x 40: 33 whole, 41 in 2), unless
+//         two rows just fill the chip or three columns are needed anyhow and there are few CUs
+//         (120 of 128 x 128: 51 us in 3 columns, 55 in 4).
+//     Of 30 grids each for 64 batches of 24 to 150 hand frames from 88 x 88 to 256 x 256, the one
+//     taken here was 5 % off the best at the median and 25 % at most (72 of 88 x 88: 40 us in 5
+//     columns, 32 in 5 strips; in buffers that stay in the cache).
+static void patch_grid(int W, int H, int cap, double share, const GridRule &rule, int *cols, int *rows) {
+    const int U = rule.unit(), nx = (W + U - 1) / U, side = frame_max_side();
+    const bool large = W > side || H > side, some = !large && rule.heavy && rule.narrow && share >= 1.7;
     auto fits = [&](int x, int y) { return (int64_t)std::min(W, U * ((nx + x - 1) / x)) * ((H + y - 1) / y) <= cap; };
+    const int wide = std::max(1, std::min(nx, (W + 128) / 256));
+    int strips = std::min(H, (int)((large ? 2.0 : 1.125) * share / wide));
     int x = 1, y = 1;
+    if (!rule.columns) {
+        if (!large && strips <= 3) strips = (int)(share / wide);
+        while (y < H && !fits(wide, y)) ++y;
+        *cols = wide;
+        *rows = std::max(y, std::min(H, strips));
+        return;
+    }
     for (y = 1; y <= H; ++y) {  // the least number of columns, in more rows where they get too narrow
         const int most = cap / ((H + y - 1) / y), units = most / U;  // widest column, in pixels and units
         x = most >= W ? 1 : units > 0 ? (nx + units - 1) / units : nx;
         if (fits(x, y) && (x == 1 || W >= (some ? 18 : 28) * x)) break;
     }
     if (y > H) y = H;  // (one row of pixels always fits)
-    const int wide = std::max(1, std::min(nx, (W + 128) / 256));
     const bool pair = share >= 2.0 && share <= 2.2;  // two rows fill one round
-    const int strips = std::min(H, (int)((large ? 2.0 : 1.125) * share / wide));
-    const int least = large || pair || !heavy ? 1 : x * y <= 2 && share >= 3.1 ? 3 : 5;
+    const int least = large || pair || !rule.heavy ? 1 : x * y <= 2 && share >= 3.1 ? 3 : 5;
     if (strips >= least && wide * strips > x * y && fits(wide, strips)) {
         x = wide;
         y = strips;
     } else if (some && y == 1 && (x < 3 || share >= 2.45)) {
-        x = std::max(x, std::min({nx, W / 18, (int)(1.9 * share)}));
+        const int more = std::min({nx, W / 18, (int)(1.9 * share)});
+        if (more > x && (more > 2 || share >= 2.0)) x = more;
     }
     *cols = x;
     *rows = y;
@@ -412,20 +435,21 @@ struct PatchCuts {
     std::vector<int32_t> cell;   // per item
 };
 
-static void cut_frame(const FrameInfo &fi, int32_t f, int cap, double share, bool heavy, bool narrow,
-                      PatchCuts &cuts, std::vector<PatchItem> &out) {
+static void cut_frame(const FrameInfo &fi, int32_t f, int cap, double share, const GridRule &rule, PatchCuts &cuts,
+                      std::vector<PatchItem> &out) {
     int px, py;
-    patch_grid(fi.width, fi.height, cap, share, heavy, narrow, &px, &py);
-    const int nx = (fi.width + 3) / 4;
-    static_assert(ORRB_MAX_DIM < 1 << 16, "sizes and grids pack into 16 bits each");
-    const uint64_t key = (uint64_t)fi.width << 48 | (uint64_t)fi.height << 32 | (uint64_t)px << 16 | (uint64_t)py;
+    patch_grid(fi.width, fi.height, cap, share, rule, &px, &py);
+    const int U = rule.unit(), nx = (fi.width + U - 1) / U;
+    static_assert(ORRB_MAX_DIM < 1 << 15, "sizes, grids and the unit pack into 64 bits");
+    const uint64_t key = (uint64_t)rule.columns << 63 | (uint64_t)fi.width << 48 | (uint64_t)fi.height << 32 |
+                         (uint64_t)px << 16 | (uint64_t)py;
     const auto [at, fresh] = cuts.first.try_emplace(key, cuts.cells.size(), cuts.cells.size() + (size_t)px * py);
     for (int y = 0; fresh && y < py; ++y)
         for (int x = 0; x < px; ++x) {
             PatchItem it{};
-            it.x0 = (uint16_t)(4 * ((int64_t)nx * x / px));
+            it.x0 = (uint16_t)(U * ((int64_t)nx * x / px));
             it.y0 = (uint16_t)((int64_t)fi.height * y / py);
-            it.x1 = (uint16_t)std::min<int64_t>(4 * ((int64_t)nx * (x + 1) / px), fi.width);
+            it.x1 = (uint16_t)std::min<int64_t>(U * ((int64_t)nx * (x + 1) / px), fi.width);
             it.y1 = (uint16_t)((int64_t)fi.height * (y + 1) / py);
             it.parts = px * py;
             const double dx = std::fabs((it.x0 + it.x1) / (double)fi.width - 1.0);
@@ -440,21 +464,76 @@ static void cut_frame(const FrameInfo &fi, int32_t f, int cap, double share, boo
     }
 }
 
+// Whether frame f's geometry is worth sharing out finely and the batch's rounds can be foreseen:
+// 2,048 triangles and more held in LDS, frames of one cost (231 mixed frames: 216 us without and
+// 230 with the finer grids, 322: 267 and 276, 131 frames of one capsule: 20.3 and 21.5).
+static bool heavy_frame(const orrb_layout *L, int32_t f, bool uniform) {
+    return uniform && L->scene_tris[L->frames[f].scene] >= 2048;
+}
+
+// Frames of which strips repeat little geometry and columns would be narrow.
+static bool tall_frame(const FrameInfo &fi) { return 4 * fi.width < 3 * fi.height; }
+
+// Parts that the lean plan cuts frame f into, one of n alike.
+static int lean_parts(const orrb_layout *L, int32_t f, int64_t n) {
+    const FrameInfo &fi = L->frames[f];
+    const double n_cu = L->ctx ? L->ctx->n_cu : 256;
+    int x, y;
+    patch_grid(fi.width, fi.height, patch_max_pixels(false), n_cu / (double)n,
+               GridRule{true, true, L->total_pixels <= 8 << 20}, &x, &y);
+    return x * y;
+}
+
+// Whether n frames of that many parts each run in rounds that are about full, so that they beat
+// the frame kernel also when they write much: two parts in one round, three and four in two,
+// five in two and a half; with more parts rounds matter less.  Hands, frame kernel / columns:
+// 88 x 88 (2 parts from 151 frames on) 150 frames 58 / 46, 152 58 / 66; 128 x 128 (3) 152 74 /
+// 53, 176 75 / 70; 144 x 144 (4) 128 80 / 64, 144 80 / 80; 160 x 160 (5) 128 86 / 70, 152 86 / 87;
+// 200 x 200 (7, rgb and visibility) 176 109 / 103, 192 109 / 110; 256 x 256 (10) 152 167 / 141, 204
+// 167 / 183.
+static bool even_rounds(const orrb_layout *L, int32_t f, int64_t n) {
+    constexpr double rounds[7] = {1.0, 1.0, 1.0, 2.0, 2.0, 2.5, 3.0};
+    const int64_t n_cu = L->ctx ? L->ctx->n_cu : 256;
+    const int parts = lean_parts(L, f, n);
+    return parts < 7 ? (double)(n * parts) <= rounds[parts] * n_cu : (parts < 9 ? 1.33 : 1.5) * n <= n_cu;
+}
+
+// Cost of n frames alike (from f on) as patches over their cost as whole frames, where more than
+// one patch holds a frame; patches pay while it is less than the CUs over n.  Lines with both sides
+// measured, us, frame kernel / patches, in buffers that are new in every call:
+//   - lean plan: 192 frames (200 x 200, depth 91 / 82, 204: 91 / 94; 128 x 128, depth 204: 63 / 57),
+//     two parts only in one round (even_rounds);
+//   - spot lights, where shading outweighs the rest: 196 (lit and textured frames of 200 x 200, 192
+//     344 / 284, 204 350 / 310; without textures 204 304 / 321);
+//   - heavy scenes in strips: 134 (128 of 224 x 224 125 / 112, 152: 126 / 133; 128 of 160 x 160 86 / 75,
+//     144: 86 / 90); beyond 230 x 230, where the frame kernel's bins overflow, 150 (152 of 256 x 256
+//     167 / 155, 176: 168 / 183); tall frames, whose strips repeat little, 196 (204 of 30 x 256 89 /
+//     82, of 40 x 230 level);
+//   - others, in strips: 204 (204 of 200 x 200 boxes 143 / 100, of 128 x 128 60 / 48, far away 36 / 31).
+static double patch_part(const orrb_layout *L, int32_t f, int64_t n, bool heavy, bool lean) {
+    const FrameInfo &fi = L->frames[f];
+    if (lean) return lean_parts(L, f, n) == 2 ? 2.0 : 1.33;
+    if (L->n_spot > 0 || (heavy && tall_frame(fi))) return 1.3;
+    return !heavy ? 1.25 : fi.width * fi.height > 230 * 230 ? 1.7 : 1.9;
+}
+
 // Move the frames that are better rendered as patches from `frames` (LDS-held scenes, in
 // order) to `patched`.  Frames beyond the frame kernel's 256 x 256 always are.  The frame
 // kernel renders one frame per CU and round and a batch takes as long as its longest; a
-// frame's patches together cost about 1.25 times a frame (they repeat geometry), or 0.75
+// frame's patches together cost patch_part times a frame (they repeat geometry), or 0.75
 // times when one patch holds it (no staging, sixteen compute waves), but fill the chip.  So
 // the frames of a batch smaller than the chip are cut when that work, spread over the CUs,
-// takes less than the longest frame, and so are the frames of a uniform batch's last,
-// partly filled round.  Measured (one MI355X, hand scenes, us, frame kernel / patches): 12
-// frames of 200 x 200 108 / 23, 48: 110 / 44, 120: 117 / 76, 200: 120 / 122; 128 x 128: 48
-// frames 74 / 33, 200: 80 / 76; 64 x 64: 24 frames 50 / 20, 200: 53 / 39.
-static void choose_patches(const orrb_layout *L, std::vector<int32_t> &frames, bool scratch, std::vector<int32_t> &patched) {
+// takes less than the longest frame (12 hand frames of 200 x 200 108 us whole, 23 as patches, 48:
+// 110 / 44; 128 x 128: 48 frames 74 / 33; 64 x 64: 24 frames 50 / 20, 200: 53 / 39), and so are the
+// frames of a uniform batch's last, partly filled round up to a quarter of the CUs (hands, 44
+// frames over: 1.15 to 1.3 times as fast, 84: 1.05 to 1.15, 144: 0.85 to 1.0; far away, where the
+// frame kernel's rounds overlap, 44: 0.9 to 1.1, 84: 0.85 to 1.1).
+static void choose_patches(const orrb_layout *L, std::vector<int32_t> &frames, bool scratch, bool lean,
+                           std::vector<int32_t> &patched) {
     const int64_t n_cu = L->ctx ? L->ctx->n_cu : 256;
     const int side = frame_max_side();
     std::vector<int32_t> rest;
-    double sum = 0.0, most = 0.0;
+    double sum = 0.0, one = 0.0, most = 0.0;
     bool uniform = true;
     for (int32_t f : frames) {
         const FrameInfo &fi = L->frames[f];
@@ -464,17 +543,21 @@ static void choose_patches(const orrb_layout *L, std::vector<int32_t> &frames, b
         }
         const double c = frame_cost(L, f, false);
         uniform = uniform && (rest.empty() || c == most);
-        sum += c * (fi.width * fi.height <= patch_max_pixels(false) ? 0.75 : 1.25);
+        one += fi.width * fi.height <= patch_max_pixels(false) ? c : 0.0;
+        sum += c;
         most = std::max(most, c);
         rest.push_back(f);
     }
+    const bool heavy = !rest.empty() && heavy_frame(L, rest[0], uniform);
+    const double part = rest.empty() ? 1.0 : patch_part(L, rest[0], (int64_t)rest.size(), heavy, lean);
+    sum = 0.75 * one + part * (sum - one);
     frames.clear();
     const int64_t n = (int64_t)rest.size();
     int64_t keep = n;  // frames that stay with the frame kernel
     if (!scratch && n > 0) {
         if (n <= n_cu || (uniform && sum <= 0.75 * n * most)) {
             if (sum < (double)n_cu * most || sum <= 0.75 * n * most) keep = 0;
-        } else if (uniform && 1.25 * (double)(n % n_cu) < (double)n_cu) {
+        } else if (uniform && 4 * (n % n_cu) <= n_cu) {
             keep = n - n % n_cu;
         }
     }
@@ -484,7 +567,8 @@ static void choose_patches(const orrb_layout *L, std::vector<int32_t> &frames, b
 
 // The patches of the frames `patched` (scenes held in LDS) and `gpatched` (larger ones): the CUs
 // are shared out by estimated work.
-static void schedule_patches(orrb_layout *L, const std::vector<int32_t> &patched, const std::vector<int32_t> &gpatched) {
+static void schedule_patches(orrb_layout *L, FramePlan &plan, const std::vector<int32_t> &patched,
+                             const std::vector<int32_t> &gpatched, bool lean) {
     const int64_t n_cu = L->ctx ? L->ctx->n_cu : 256;
     std::vector<PatchItem> items;
     PatchCuts cuts;
@@ -495,15 +579,15 @@ static void schedule_patches(orrb_layout *L, const std::vector<int32_t> &patched
         uniform = uniform && frame_cost(L, f, false) == frame_cost(L, patched[0], false);
     }
     for (int32_t f : gpatched) total += frame_cost(L, f, true);
-    int64_t pixels = 0;
-    for (const FrameInfo &fi : L->frames) pixels += (int64_t)fi.width * fi.height;
     for (int32_t f : gpatched)
-        cut_frame(L->frames[f], f, patch_max_pixels(true), (double)n_cu * frame_cost(L, f, true) / total, false, false,
-                  cuts, items);
+        cut_frame(L->frames[f], f, patch_max_pixels(true), (double)n_cu * frame_cost(L, f, true) / total,
+                  GridRule{false, true, false}, cuts, items);
     L->gp_items = (int64_t)items.size();
-    for (int32_t f : patched)
+    for (int32_t f : patched) {
+        const bool heavy = heavy_frame(L, f, uniform);
         cut_frame(L->frames[f], f, patch_max_pixels(false), (double)n_cu * frame_cost(L, f, false) / total,
-                  uniform && L->scene_tris[L->frames[f].scene] >= 2048, pixels <= 8 << 20, cuts, items);
+                  GridRule{heavy, heavy && (lean || L->n_spot > 0), L->total_pixels <= 8 << 20}, cuts, items);
+    }
     // The middle of a frame usually shows the most: patches nearest to their frame's centre
     // first, so that the last ones to run are light, and the same patch of consecutive
     // frames on consecutive XCDs (in frame order, eight patches a frame put all the middle
@@ -511,17 +595,18 @@ static void schedule_patches(orrb_layout *L, const std::vector<int32_t> &patched
     std::vector<size_t> next(kPatchRanks + 1, 0);  // items by rank, in frame order within one
     for (int32_t c : cuts.cell) ++next[cuts.rank[c] + 1];
     for (int r = 0; r < kPatchRanks; ++r) next[r + 1] += next[r];
-    L->pitems.resize(items.size());
-    for (size_t k = 0; k < items.size(); ++k) L->pitems[next[cuts.rank[cuts.cell[k]]]++] = items[k];
+    plan.pitems.resize(items.size());
+    for (size_t k = 0; k < items.size(); ++k) plan.pitems[next[cuts.rank[cuts.cell[k]]]++] = items[k];
+    plan.p_frames = (int64_t)patched.size();
     // Counter sums, for frames that the frame kernel could take, where several patches share
     // one (with more frames than CUs only those of a last round: at most as many as CUs).
-    L->account_slots = 0;
     const int side = frame_max_side();
-    for (const PatchItem &it : L->pitems) {
+    for (const PatchItem &it : plan.pitems) {
         FrameInfo &fi = L->frames[it.frame];
         if ((it.x0 | it.y0) != 0 || fi.n_obj == 0 || fi.width > side || fi.height > side) continue;
         if (fi.mode == 2 && (L->tuning.path != 2 || L->fits[it.frame] != 2)) continue;
-        fi.account = it.parts > 1 ? (int32_t)L->account_slots++ : kOnePatch;
+        if (it.parts > 1 && fi.account < 0) fi.account = (int32_t)L->account_slots++;
+        if (fi.account < 0) fi.account = kOnePatch;
     }
 }
 
@@ -534,14 +619,14 @@ static int64_t render_kernels(const orrb_layout *L) {
     int64_t n = L->shadow ? 1 + render_kernels(L->shadow) : 0;
     if (!L->vitems.empty() || !L->titems.empty()) n += 1;
     if (!L->titems.empty()) n += 1;
-    if (!L->fitems.empty()) n += 1 + L->f_dynamic;
-    n += patch_launches((int64_t)L->pitems.size());
+    if (!L->plan[0].fitems.empty()) n += 1 + L->plan[0].f_dynamic;
+    n += patch_launches((int64_t)L->plan[0].pitems.size());
     return n;
 }
 
 static WsLayout ws_layout(const orrb_layout *L) {
     const FrameScratch fs =
-        frame_scratch(L->gframes, L->f_frames, L->gf_verts, L->gf_tris, L->tuning.bin_cap,
+        frame_scratch(L->gframes, (int64_t)L->plan[0].fitems.size(), L->gf_verts, L->gf_tris, L->tuning.bin_cap,
                       L->ctx ? L->ctx->n_cu : 256);
     return ws_layout(L->tiled_vertex_instances, L->tiled_object_instances, fs, L->account_slots);
 }
@@ -627,13 +712,13 @@ static bool frame_scratch_pays(const orrb_layout *L) {
 static void build_items(orrb_layout *L) {
     L->titems.clear();
     L->vitems.clear();
-    L->fitems.clear();
+    std::vector<int32_t> whole;
     const int TW = L->tuning.tile_w, TH = L->tuning.tile_h;
     int64_t vi = 0, oi = 0;
     L->gframes = L->gf_verts = L->gf_tris = L->gp_tris = 0;
     const int path = L->tuning.path;
     const bool scratch = path == 2 && frame_scratch_pays(L);
-    std::vector<int32_t> patched, gpatched;
+    std::vector<int32_t> gpatched;
     for (int64_t f = 0; f < L->n_frames; ++f) {
         FrameInfo &fi = L->frames[f];
         fi.tiles_x = (fi.width + TW - 1) / TW;
@@ -642,11 +727,11 @@ static void build_items(orrb_layout *L) {
         fi.vbase = 0;
         fi.oi_base = 0;
         if (path != 1 && L->fits[f] == 1) {
-            L->fitems.push_back((int32_t)f);
+            whole.push_back((int32_t)f);
             continue;
         }
         if (scratch && L->fits[f] == 2) {
-            L->fitems.push_back((int32_t)f);
+            whole.push_back((int32_t)f);
             fi.mode = 1;
             L->gframes++;
             L->gf_verts = std::max<int64_t>(L->gf_verts, L->scene_verts[fi.scene]);
@@ -669,11 +754,46 @@ static void build_items(orrb_layout *L) {
     }
     L->tiled_vertex_instances = vi;
     L->tiled_object_instances = oi;
-    choose_patches(L, L->fitems, L->gframes > 0, patched);
-    schedule_frames(L);
-    schedule_patches(L, patched, gpatched);
-    L->p_frames = (int64_t)patched.size();
     L->gp_frames = (int64_t)gpatched.size();
+    L->account_slots = 0;
+    double sum = 0.0;
+    bool uniform = true;
+    for (int32_t f : whole) {
+        sum += frame_cost(L, f, false);
+        uniform = uniform && frame_cost(L, f, false) == frame_cost(L, whole[0], false);
+    }
+    const int64_t n = (int64_t)whole.size(), n_cu = L->ctx ? L->ctx->n_cu : 256;
+    // Two plans for heavy scenes alike: columns for calls that write little, strips or whole frames
+    // for the others.  Columns pay while their writes (about 1.9 TB/s) take no longer than the
+    // geometry (hands: 150 cost units a CU and us), or up to 64 MB, a quarter of the memory-side
+    // cache.  (In a batch of more frames than CUs what the whole frames write counts.)  Hands,
+    // us, columns / strips (bytes over that time): 128 frames of 128 x 128 (1.14 MB a us) 50 / 56, of
+    // 160 x 160 (1.57) 70 / 75, 96 of 200 x 200 (2.1) 75 / 67, 72 of 224 x 224 (2.4) 70 / 59.  Grading
+    // and Tracker records are work of their own (every output, 144 of 128 x 128, 1.8 MB a us: 87
+    // / 108).  Where the rounds come out uneven, only calls that write much less keep ahead of the
+    // frame kernel (192 of 128 x 128: rgb and visibility, 0.7 MB a us, 74 whole, 65 in columns;
+    // four channels, 1.1: 76 and 75).
+    L->lean_bytes[0] = L->lean_bytes[1] = 0;
+    if (n > 0 && n <= n_cu && n == L->n_frames && L->n_spot == 0 && heavy_frame(L, whole[0], uniform) &&
+        !tall_frame(L->frames[whole[0]])) {
+        const bool even = even_rounds(L, whole[0], n);
+        const double geometry = sum / (150.0 * n_cu);  // us
+        const int64_t cache = even ? 64 << 20 : 0;
+        const int64_t most = std::max(cache, (int64_t)((even ? 1.75e6 : 0.8e6) * geometry));
+        if (3 * L->total_pixels <= most) {  // some call can write as little
+            L->lean_bytes[0] = most;
+            L->lean_bytes[1] = std::max(cache, (int64_t)((even ? 2.45e6 : 0.0) * geometry));
+        }
+    }
+    for (int lean = 0; lean < (L->lean_bytes[0] > 0 ? 2 : 1); ++lean) {
+        FramePlan &plan = L->plan[lean];
+        std::vector<int32_t> patched;
+        plan.fitems = whole;
+        choose_patches(L, plan.fitems, L->gframes > 0, lean != 0, patched);
+        schedule_frames(L, plan);
+        schedule_patches(L, plan, patched, gpatched, lean != 0);
+    }
+    if (L->lean_bytes[0] == 0) L->plan[1] = FramePlan();
 }
 
 // Tables of the shading adjoint (independent of the tuning).
@@ -769,8 +889,10 @@ static orrb_status upload_layout(orrb_layout *L) {
     L->o_objs = P.add(L->objs);
     L->o_vitems = P.add(L->vitems);
     L->o_titems = P.add(L->titems);
-    L->o_fitems = P.add(L->fitems);
-    L->o_pitems = P.add(L->pitems);
+    for (FramePlan &plan : L->plan) {
+        plan.o_fitems = P.add(plan.fitems);
+        plan.o_pitems = P.add(plan.pitems);
+    }
     L->o_light_type = P.add(L->light_type);
     if (L->n_spot > 0) {
         L->o_spot_slot = P.add(L->spot_slot);
@@ -1156,7 +1278,7 @@ orrb_status orrb_layout_create(orrb_context *ctx, const orrb_layout_desc *d, orr
     L->all_vertex_instances = vi;
     L->all_object_instances = oi;
     build_items(L);
-    if (std::max({L->titems.size(), L->vitems.size(), L->pitems.size()}) > 0x7fffffff) {
+    if (std::max({L->titems.size(), L->vitems.size(), L->plan[0].pitems.size()}) > 0x7fffffff) {
         delete L;
         return fail(ORRB_ERR_UNSUPPORTED, "too many tiles");
     }
@@ -1232,7 +1354,7 @@ orrb_status orrb_layout_info_get(const orrb_layout *L, orrb_layout_info *info) {
     // larger scenes' patches count as the tiled path's under path 0, as the frame path's under 2
     const bool gp_tiled = L->tuning.path != 2;
     info->tile_items = (int64_t)(L->titems.size() + (gp_tiled ? L->gp_items : 0));
-    info->frame_path_frames = L->f_frames + L->p_frames + (gp_tiled ? 0 : L->gp_frames);
+    info->frame_path_frames = (int64_t)L->plan[0].fitems.size() + L->plan[0].p_frames + (gp_tiled ? 0 : L->gp_frames);
     info->workspace_bytes = call_ws(L).total;
     info->workspace_bytes_any = ws_bytes_any(L);
     if (L->shadow) info->workspace_bytes_any += call_ws(L, ws_bytes_any(L->shadow)).total - ws_layout(L).total + 256;
@@ -1268,7 +1390,8 @@ orrb_status orrb_layout_set_tuning(orrb_layout *L, const orrb_tuning *t) {
 size_t orrb::render_workspace_bytes(const orrb_layout *L) { return call_ws(L).total; }
 
 PathUse orrb::layout_use(const orrb_layout *L) {
-    PathUse u{!L->titems.empty(), !L->fitems.empty() || !L->pitems.empty(), L->gframes > 0};
+    const FramePlan &plan = L->plan[0];
+    PathUse u{!L->titems.empty(), !plan.fitems.empty() || !plan.pitems.empty(), L->gframes > 0};
     if (L->shadow) {
         const PathUse s = layout_use(L->shadow);
         u = {u.tiled || s.tiled, u.other || s.other, u.scratch || s.scratch};
@@ -1278,6 +1401,12 @@ PathUse orrb::layout_use(const orrb_layout *L) {
 
 size_t orrb::patch_sum_bytes(const orrb_layout *L) {
     return al256(sizeof(uint64_t) * (size_t)L->account_slots) + (L->shadow ? patch_sum_bytes(L->shadow) : 0);
+}
+
+// Bytes a call writes per pixel.
+static int64_t out_bytes(const orrb_outputs *o) {
+    return (o->rgb ? 12 : 0) + (o->depth ? 4 : 0) + (o->normal ? 12 : 0) + (o->seg ? 4 : 0) + (o->tri_id ? 4 : 0) +
+           (o->vis ? 8 : 0) + (o->alpha ? 4 : 0) + (o->rgb8 ? 3 : 0);
 }
 
 // A render call: host checks, then the kernels on `stream`.  With `timing` false it
@@ -1326,10 +1455,13 @@ orrb_status orrb::render_impl(orrb_context *ctx, const orrb_layout *L, const orr
     a.frames = L->tab.at<FrameInfo>(L->o_frames);
     a.vitems = L->tab.at<int2>(L->o_vitems);
     a.titems = L->tab.at<int2>(L->o_titems);
-    a.fitems = L->tab.at<int32_t>(L->o_fitems);
-    a.n_fitems = (int32_t)L->fitems.size();
-    a.f_grid = L->f_grid;
-    a.f_dynamic = L->f_dynamic;
+    const int64_t lean_bytes = L->lean_bytes[out->alpha || out->track || out->rgb8];
+    const bool lean = lean_bytes > 0 && out_bytes(out) * L->total_pixels <= lean_bytes;
+    const FramePlan &plan = L->plan[lean];
+    a.fitems = L->tab.at<int32_t>(plan.o_fitems);
+    a.n_fitems = (int32_t)plan.fitems.size();
+    a.f_grid = plan.f_grid;
+    a.f_dynamic = plan.f_dynamic;
     a.n_vitems = (int32_t)L->vitems.size();
     a.v_wave = vertex_by_wave(L, a.n_vitems);
     a.n_titems = (int32_t)L->titems.size();
@@ -1388,7 +1520,7 @@ orrb_status orrb::render_impl(orrb_context *ctx, const orrb_layout *L, const orr
     for (int k = 0; k < 3 && e == hipSuccess; ++k) {
         if (k == 0 && a.n_titems == 0 && a.n_vitems == 0) continue;  // no frame needs k_vertex
         if (k == 1 && a.n_titems == 0) continue;
-        if (k == 2 && a.n_fitems == 0 && L->pitems.empty()) continue;
+        if (k == 2 && a.n_fitems == 0 && plan.pitems.empty()) continue;
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (T.enabled && timing) {
             e0 = T.get();
@@ -1398,8 +1530,8 @@ orrb_status orrb::render_impl(orrb_context *ctx, const orrb_layout *L, const orr
         if (e == hipSuccess)
             e = k == 0 ? launch_vertex(a, st) : k == 1 ? launch_raster(a, st, ctx->n_cu) : launch_frame(a, st, ctx->n_cu);
         if (k == 2 && e == hipSuccess) {
-            a.pitems = L->tab.at<PatchItem>(L->o_pitems);
-            a.n_pitems = (int32_t)L->pitems.size();
+            a.pitems = L->tab.at<PatchItem>(plan.o_pitems);
+            a.n_pitems = (int32_t)plan.pitems.size();
             a.n_account = (int32_t)L->account_slots;
             frame_limits(&a.p_limits[0].bin_max, &a.p_limits[0].surv_max);
             if (L->tuning.path == 2) {  // the frame kernel's global scratch would have had these limits
@@ -1407,8 +1539,8 @@ orrb_status orrb::render_impl(orrb_context *ctx, const orrb_layout *L, const orr
                 a.p_limits[1].bin_max = (int32_t)std::min<int64_t>(fs.bins, 0x7fffffff);
                 a.p_limits[1].surv_max = (int32_t)fs.surv;
             }
-            if (out->stats && (L->p_frames > 0 || L->tuning.path == 2)) a.p_account = (unsigned long long *)(ws + w.account);
-            e = launch_patch(a, L->p_frames == 0 ? 1 : L->gp_frames == 0 ? 0 : 2, st);
+            if (out->stats && (plan.p_frames > 0 || L->tuning.path == 2)) a.p_account = (unsigned long long *)(ws + w.account);
+            e = launch_patch(a, plan.p_frames == 0 ? 1 : L->gp_frames == 0 ? 0 : 2, st);
         }
         if (T.enabled && timing && e0 && e1 && e == hipSuccess) {
             e = hipEventRecord(e1, st);

@@ -8,11 +8,11 @@ import pytest
 
 from paper_1906_11633_amd import scenes as S
 from tests.test_frame_groups_gpu import FRAMES, _repeat
-from tests.test_patches_gpu import _both, renderer  # noqa: F401
+from tests.test_patches_gpu import TILED, _both, _resized, renderer  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
-WHOLE, PATCHES, SPLIT = (1, False), (1, True), (2, True)  # launches, sums
+WHOLE, PATCHES, SPLIT = (1, False), (1, True), (2, True)  # launches, sums (of calls with few or many bytes to write)
 
 
 def _check(renderer, b, name, tuning, kind):  # noqa: F811
@@ -28,6 +28,24 @@ def _check(renderer, b, name, tuning, kind):  # noqa: F811
             assert np.array_equal(got[k], want[k]), (name, k, int((got[k] != want[k]).sum()))
     assert got["stats"][0] == 0
     return got["stats"]
+
+
+def _few_outputs(renderer, b):  # noqa: F811
+    """Depth alone and 8-bit RGB alone, which write few bytes, against the tiled path."""
+    import torch
+    b = S.with_postprocessing(b, seed=3)
+    for kw in (dict(base=("depth",)), dict(base=(), rgb8=True)):
+        got = []
+        for tuning in ((32, 32, 512, 0, 0), TILED):
+            job = renderer.prepare(b)
+            job.layout.set_tuning(*tuning)
+            out = renderer.alloc_outputs(job, **kw)
+            for t in out.values():
+                t.view(torch.uint8).fill_(0x5a)
+            got.append(renderer.render(job, out))
+        torch.cuda.synchronize()
+        for k in got[0]:
+            assert torch.equal(got[0][k].view(torch.uint8), got[1][k].view(torch.uint8)), k
 
 
 def test_survivor_overflow_of_whole_frames(renderer):  # noqa: F811
@@ -83,9 +101,14 @@ def test_scratch_bins_of_whole_frames(renderer, quads):  # noqa: F811
     assert st[1] == (FRAMES if entries > bins else 0), st
 
 
-@pytest.mark.parametrize("frames,kind", [(204, PATCHES), (205, WHOLE), (256, WHOLE), (257, SPLIT), (460, SPLIT), (461, WHOLE),
-                                         (512, WHOLE)])
-def test_rounds_of_a_uniform_batch(renderer, frames, kind):  # noqa: F811
-    """Frames of more than one patch (90 x 90): all patches, whole frames, or whole rounds and the
-    rest as patches.  256 CUs."""
-    _check(renderer, S.config2(12, frames, 90, 1), f"{frames} frames", (32, 32, 512, 0, 0), kind)
+@pytest.mark.parametrize("size,frames,kind", [
+    ((90, 90), 134, PATCHES), ((90, 90), 135, PATCHES), ((90, 90), 150, PATCHES), ((90, 90), 151, WHOLE), ((90, 90), 256, WHOLE),
+    ((90, 90), 257, SPLIT), ((90, 90), 320, SPLIT), ((90, 90), 321, WHOLE), ((90, 90), 512, WHOLE),
+    ((200, 200), 134, PATCHES), ((200, 200), 135, PATCHES), ((200, 200), 192, PATCHES), ((200, 200), 193, WHOLE),
+    ((200, 200), 320, SPLIT), ((200, 200), 321, WHOLE)])
+def test_rounds_of_a_uniform_batch(renderer, size, frames, kind):  # noqa: F811
+    """Frames of more than one patch: all patches (of one cut or another, by the bytes that a call
+    writes), whole frames, or whole rounds and the rest as patches.  256 CUs."""
+    b = _resized(S.config2(12, frames, 90, 1), [size])
+    _check(renderer, b, f"{frames} frames of {size}", (32, 32, 512, 0, 0), kind)
+    _few_outputs(renderer, b)
