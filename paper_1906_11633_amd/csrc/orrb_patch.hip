@@ -1,5 +1,6 @@
 // Patch path (k_patch): rectangles of frames, for batches with too few frames to occupy the
-// chip with one workgroup per frame and for frames larger than the frame kernel takes.
+// chip with one workgroup per frame, for frames larger than the frame kernel takes and for
+// scenes that do not fit in LDS.
 //
 // One 1024-thread workgroup renders one patch.  Scenes that fit in LDS (the frame kernel's
 // limits) need no intermediate data in global memory; for larger ones (G) k_vertex has put
@@ -28,9 +29,9 @@
 // pixel centres); one lane steps through at most kPOwn pixels because a longer loop keeps
 // the other 63 waiting (8 to 12 measured alike, 32 up to 15 % slower).
 // One MI355X, us a call, one workgroup per frame before / patches: 4 plain 64 x 64 frames
-// 27 / 9.5, 6 hand frames of 128 x 128 68 / 16, 48 of 200 x 200 118 / 49; 2 of 1024 x 768
+// 27 / 9.5, 6 hand frames of 128 x 128 68 / 16, 48 of 200 x 200 118 / 45; 2 of 1024 x 768
 // (tiled path before) 113 / 30.  Larger scenes (G), 24 / 192 / 384 uneven frames: tiled path
-// 132 / 387 / 683, frame kernel with global scratch 175 / 365 / 382, patches 54 / 172 / 276.
+// 132 / 387 / 683, frame kernel with global scratch 175 / 365 / 382, patches 47 / 146 / 256.
 #include <cstddef>
 
 #include "orrb_post.h"
